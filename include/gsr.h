@@ -79,10 +79,9 @@ typedef struct {
    *    the order of those additions, and so the last bits of the gradients,
    *    varies between runs).
    * 1: the backward stores every (Gaussian, tile, 8x8 pixel block) partial
-   *    sum (4x4 quadrant when only the pose gradient is wanted) and adds them
-   *    per Gaussian in a fixed order (tiles in row-major order of its tile
-   *    rectangle, blocks in order), so
-   *    gradients are bitwise reproducible; it needs 648 bytes per tile
+   *    sum and adds them per Gaussian in a fixed order (tiles in row-major
+   *    order of its tile rectangle, blocks in order), so
+   *    gradients are bitwise reproducible; it needs 168 bytes per tile
    *    overlap and 4 per Gaussian and view more device memory, allocated by
    *    the first such backward of a state (synchronises), and is slower.
    *    Not supported by the tracking graph (GSR_EINVAL). */

@@ -61,8 +61,8 @@ struct gsr_state {
   uint32_t* det_total = nullptr;  // [1]
   uint32_t* det_scan = nullptr;   // scan temp
   uint32_t* det_rev = nullptr;    // [K] list position of each (record, tile of its rectangle)
-  uint32_t* det_mask = nullptr;   // [K] quadrants that stored a sum
-  float* det_part = nullptr;      // [K, 16, 10] per (list position, quadrant) sums
+  uint32_t* det_mask = nullptr;   // [K] blocks that stored a sum
+  float* det_part = nullptr;      // [K, 4, 10] per (list position, 8x8 block) sums
 };
 
 struct gsr_track_graph {
@@ -176,7 +176,7 @@ void carve_A(gsr_state* s, char* base, int64_t n, int64_t P, int64_t tiles, int6
   s->bin_T = c.take<uint32_t>(tiles);
   s->bin_R = c.take<int2>(tiles);
   s->bin_ticket = c.take<uint32_t>(4);
-  s->g2d = c.take<float>(10 * n);
+  s->g2d = c.take<float>(10 * (n + std::min<int64_t>(n, gsr::kWideSums)));  // doubles for small sets
   s->Tfin = c.take<float>(P);
   s->last = c.take<int>(P);
   s->ranges = c.take<int2>(tiles);
@@ -220,7 +220,7 @@ int ensure_A(gsr_ctx* c, gsr_state* s, int64_t n, int64_t P, int64_t tiles, int6
   // The per-Gaussian backward sums start at zero and every backward leaves them
   // at zero (the projection backward clears what it reads), so they are
   // cleared only here, when the workspace is allocated.
-  gsr::launch_fill_f32(s->g2d, 0.f, 10 * nn, c->stream);
+  gsr::launch_fill_f32(s->g2d, 0.f, 10 * (nn + std::min<int64_t>(nn, gsr::kWideSums)), c->stream);
   // likewise the binning's tile totals and ticket (the counting pass's last
   // workgroup returns them to zero)
   gsr::launch_fill_u32(s->bin_T, 0u, tt, c->stream);
@@ -266,7 +266,7 @@ int ensure_D(gsr_ctx* c, gsr_state* s) {
     s->det_scan = cv.take<uint32_t>(gsr::scan_temp_words(nn));
     s->det_rev = cv.take<uint32_t>(kk);
     s->det_mask = cv.take<uint32_t>(kk);
-    s->det_part = cv.take<float>(kk * 16 * 10);
+    s->det_part = cv.take<float>(kk * 4 * 10);
     if (pass == 0) {
       void* p = nullptr;
       if (hipMalloc(&p, cv.off) != hipSuccess) {
@@ -410,12 +410,13 @@ void enqueue_bwd(gsr_ctx* c, gsr_state* s, hipStream_t st, const float* gC, cons
   // s->g2d is zero here: cleared when allocated, and each projection backward
   // clears the sums it reads
   const bool geom_only = !adam && (!grads || (!grads->opacities && !grads->colors));
+  const bool wide = !s->det && s->n * s->n_views <= gsr::kWideSums;
   gsr::BwdArgs ba{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz, s->Tfin, s->last,
-                  gC, gD, gA, s->g2d, geom_only, n_items, s->queue, s->blocks > 0 ? s->order : nullptr, s->blocks,
+                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, s->blocks > 0 ? s->order : nullptr, s->blocks,
                   nullptr, nullptr};
   if (s->det) {
     // arena D is in place (ensure_D): list positions of every (record, tile),
-    // then the stored quadrant sums, then their fixed-order totals
+    // then the stored block sums, then their fixed-order totals
     const int64_t n_rec = s->n * s->n_views;
     Stage t(c, "render_bwd");
     gsr::launch_exclusive_scan(s->counts, s->det_goff, n_rec, s->det_total, s->det_scan, st);
@@ -432,7 +433,7 @@ void enqueue_bwd(gsr_ctx* c, gsr_state* s, hipStream_t st, const float* gC, cons
   gsr_grads none{};
   const gsr_grads& G = grads ? *grads : none;
   gsr::ProjectBwdArgs pb{s->n, s->g.means, s->g.scales, s->g.quats, s->g.opacities, s->g.colors, s->pose7,
-                         s->counts, s->g2d, G.means, G.scales, G.quats, G.opacities, G.colors,
+                         s->counts, wide, s->g2d, G.means, G.scales, G.quats, G.opacities, G.colors,
                          want_pose ? s->pose_acc : nullptr, s->n_views};
   if (adam) pb.adam = *adam;
   {

@@ -76,15 +76,21 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
   return x * q + (x < r ? x : r) + i;
 }
 
-// Wave-wide sums of ten per-lane values: returns the sum the lane ends with
-// and sets *f to its field, or -1 (ten lanes end with one field each).
-// Field-splitting butterfly: at each of four exchange steps a
-// lane keeps half of its remaining fields and hands the other half to its
-// partner (v_permlane32_swap across the 32-lane halves, v_permlane16_swap
-// across rows, then DPP row_mirror / row_half_mirror inside rows), so the ten
-// sums cost ~27 VALU operations instead of ten full 64-lane reductions. After
-// the last quad reduction lane L holds field 8 b2 + 4 b3 + 2 b4 + b5 of its
-// lane bits b_i.
+// The same with chunks of kXcdChunk consecutive tiles dealt to the XCDs in
+// turn: every XCD gets a share of each part of the image, so one whose part is
+// dense does not end last. The barrier-free backward is 2 to 5 % faster with
+// chunks of 4 to 16 tiles than with one run per XCD (1200x680 / 500K: 179 ->
+// 176 us, 640x480: 121 -> 118; with 48 tiles 640x480 takes 128); the
+// forward, whose workgroups share their fetches, is not.
+constexpr int kXcdChunk = 16;
+__device__ __forceinline__ int xcd_chunk(int b, int nb) {
+  const int full = nb / (8 * kXcdChunk) * (8 * kXcdChunk);
+  const int x = b & 7, i = b >> 3;
+  return b < full ? ((i / kXcdChunk) * 8 + x) * kXcdChunk + i % kXcdChunk : b;
+}
+
+// The sum of `a` over a lane pair that differs in bit 5 (bit 4) in the lane
+// whose bit is 0, and of `b` in the other one.
 __device__ __forceinline__ float perm_add32(float a, float b) {
   auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return __uint_as_float(p[0]) + __uint_as_float(p[1]);
@@ -97,35 +103,6 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
-__device__ __forceinline__ float wave_reduce10(const float v[10], int lane, int* f) {
-  // step 1 (lane bit 5): pairs of fields (2k, 2k+1)
-  const float r10 = perm_add32(v[0], v[1]);
-  const float r11 = perm_add32(v[2], v[3]);
-  const float r12 = perm_add32(v[4], v[5]);
-  const float r13 = perm_add32(v[6], v[7]);
-  const float r14 = perm_add32(v[8], v[9]);
-  // step 2 (lane bit 4)
-  const float r20 = perm_add16(r10, r11);
-  const float r21 = perm_add16(r12, r13);
-  const float r22 = perm_add16(r14, 0.f);
-  // step 3 (lane bit 3): partner = 15 - i inside the row
-  const bool b3 = (lane >> 3) & 1;
-  const float a0 = b3 ? r21 : r20, c0 = b3 ? r20 : r21;
-  const float r30 = a0 + dpp_f<0x140>(c0);                 // row_mirror
-  const float a1 = b3 ? 0.f : r22, c1 = b3 ? r22 : 0.f;
-  const float r31 = a1 + dpp_f<0x140>(c1);
-  // step 4 (lane bit 2): partner = 7 - i inside the half row
-  const bool b2 = (lane >> 2) & 1;
-  const float a2 = b2 ? r31 : r30, c2 = b2 ? r30 : r31;
-  float r4 = a2 + dpp_f<0x141>(c2);                        // row_half_mirror
-  // steps 5-6: sum the quad
-  r4 += dpp_f<0xb1>(r4);                                   // quad_perm [1,0,3,2]
-  r4 += dpp_f<0x4e>(r4);                                   // quad_perm [2,3,0,1]
-  const int fld = 8 * ((lane >> 2) & 1) + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 4) & 1) + ((lane >> 5) & 1);
-  *f = ((lane & 3) == 0 && fld < 10) ? fld : -1;
-  return r4;
-}
-
 __device__ __forceinline__ int wave_max_int(int v) {
   for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
   return v;
@@ -286,6 +263,14 @@ struct FwdArgs {
 };
 void launch_render_fwd(const Raster& R, const FwdArgs& a, hipStream_t s);
 
+// The compositing backward adds a Gaussian's sums with atomics, in an order
+// that varies from run to run. Up to this many (Gaussian, view) pairs the
+// sums are doubles, which makes the results all but independent of the order;
+// such a launch is bound by latency and does not notice (1,000 Gaussians at
+// 64x48: 16.4 us against 16.2). At 500,000 the doubled traffic of the atomics
+// and of the projection backward costs 31 us of 453, so there they are floats.
+constexpr int64_t kWideSums = 32768;
+
 struct BwdArgs {
   const int2* ranges;
   const uint32_t* ids;
@@ -295,15 +280,16 @@ struct BwdArgs {
   const float* Tfin;
   const int* last;
   const float *gC, *gD, *gA;
-  float* g2d;  // [V*n, 10]: sums of q (dx, dy, dx^2, dx dy, dy^2), q = dL/dp / ln 2; o, r, g, b, z
+  float* g2d;  // [V*n, 10] floats, or doubles if `wide`: sums of q (dx, dy, dx^2, dx dy, dy^2, 1), q = dL/dp / ln 2; r, g, b, z
+  bool wide;       // see kWideSums
   bool geom_only;  // only fields 0-4 and 9 are needed (no opacity or colour gradient wanted)
   int n_items;
   int* queue;
   const int* order;
   int blocks;
   // deterministic backward (both NULL otherwise): per (list position,
-  // quadrant of the tile) sums [K, 16, 10 or 6] and per list position the
-  // 16-bit mask of the quadrants that stored one (zero before the launch)
+  // 8x8 block of the tile) sums [K, 4, 10 or 6] and per list position the
+  // mask of the blocks that stored one (zero before the launch)
   float* part;
   uint32_t* mask;
 };
@@ -348,6 +334,7 @@ struct ProjectBwdArgs {
   const float *means, *scales, *quats, *opacities, *colors;
   const float* pose7;
   const uint32_t* counts;
+  bool wide;    // g2d holds doubles
   float* g2d;  // read, then cleared (zero again for the next backward)
   float *g_means, *g_scales, *g_quats, *g_opacities, *g_colors;  // may be NULL; summed over views
   float* pose_acc;  // [n_views][blocks][12] per-workgroup dL/dR_p (9, row-major), dL/dt (3); NULL = skip

@@ -199,7 +199,7 @@ __device__ __forceinline__ void chain_one(const Raster& Rr, const PoseF& P, cons
   const float g_a = -0.5f * G2[2];
   const float g_b = -G2[3];
   const float g_c = -0.5f * G2[4];
-  go += G2[5];
+  go += G2[5];  // sum q; divided by the opacity below (alpha = o 2^p)
   gc[0] += G2[6];
   gc[1] += G2[7];
   gc[2] += G2[8];
@@ -354,12 +354,25 @@ __global__ __launch_bounds__(256, 4) void k_project_bwd(Raster Rr, ProjectBwdArg
     for (int i = 0; i < 12; ++i) pacc[i] = 0.f;
     const int64_t o = (int64_t)v * a.n + k;
     if (k < a.n && a.counts[o] > 0) {
-      float* g2 = a.g2d + 10 * o;
-      chain_one(Rr, P, a, k, g2, gm, gs, gq, go, gc, pacc);
+      float g2[10];
       // leave the sums at zero for the next backward (the compositing backward
       // only adds to Gaussians with tiles, i.e. the ones cleared here)
+      if (a.wide) {
+        double* sums = reinterpret_cast<double*>(a.g2d) + 10 * o;
 #pragma unroll
-      for (int i = 0; i < 10; ++i) g2[i] = 0.f;
+        for (int i = 0; i < 10; ++i) {
+          g2[i] = (float)sums[i];
+          sums[i] = 0.0;
+        }
+      } else {
+        float* sums = a.g2d + 10 * o;
+#pragma unroll
+        for (int i = 0; i < 10; ++i) {
+          g2[i] = sums[i];
+          sums[i] = 0.f;
+        }
+      }
+      chain_one(Rr, P, a, k, g2, gm, gs, gq, go, gc, pacc);
     }
     if (a.pose_acc) {
 #pragma unroll
@@ -377,6 +390,7 @@ __global__ __launch_bounds__(256, 4) void k_project_bwd(Raster Rr, ProjectBwdArg
       __syncthreads();
     }
   }
+  if (go != 0.f) go /= a.opacities[k];  // the views' sums of q: dL/do = sum q / o (alpha = o 2^p)
   if (a.adam.on && a.adam.reg_w != 0.f && k < a.n) {
     float d[3];
     (void)reg_term(a.scales[3 * k], a.scales[3 * k + 1], a.scales[3 * k + 2], a.adam.reg_w, d);

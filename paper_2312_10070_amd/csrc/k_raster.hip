@@ -25,21 +25,14 @@
 // transmittance in front of Gaussian j is recomputed as T_j = T_{j+1} /
 // (1 - alpha_j) instead of being stored; suffix sums of c alpha T and z alpha
 // T give the second terms of dC/dalpha and Eq. 8. Per pair, ten partials
-// (sums of q (dx, dy, dx^2, dx dy, dy^2) with q = dL/dp / ln 2 for
-// alpha = o 2^p, then opacity, colour, direct depth) are summed over pixels
-// by DPP / permlane field-splitting reductions. Two walks:
-//  - block walk (all ten fields, mapping): batches of 512 records, one visit
-//    list per wave (records reaching its 8x8 block), walked one record at a
-//    time with the record broadcast from LDS; a wave's sums go out with one
-//    10-lane atomic per (Gaussian, wave);
-//  - quadrant walk (the six fields of a pose-only backward, tracking):
-//    batches of 256 records, one visit list per 4x4 quadrant, the four rows
-//    of a wave walking their own lists side by side; a row's sums are added
-//    to per-record accumulators in LDS, flushed with one atomic per
-//    (Gaussian, tile, field) after each batch.
-// A deterministic variant of each stores the wave's (row's) sums per (list
-// position, block or quadrant) instead and a second pass adds them per
-// Gaussian in a fixed order.
+// (sums of q (dx, dy, dx^2, dx dy, dy^2, 1) with q = dL/dp / ln 2 for
+// alpha = o 2^p, then colour and direct depth; six of them for a pose-only
+// backward) are summed over the pixels of a wave's 8x8 block, four records at
+// a time, on the matrix cores (see bwd_item), and a record's sums go out with
+// one atomic per field. Each wave fetches, tests and walks its records by
+// itself: the waves of a workgroup never wait for one another.
+// A deterministic variant stores the wave's sums per (list position, block)
+// instead and a second pass adds them per Gaussian in a fixed order.
 //
 // Launch shapes: one workgroup per item (items dealt to XCDs in contiguous
 // runs), or a persistent grid whose workgroups pull items from a counter in
@@ -50,17 +43,13 @@ namespace gsr {
 
 namespace {
 
-// Records staged in LDS per batch (forward, backward block walk, backward
-// quadrant walk), capacity of a
-// quadrant's visit list, and the LDS slot of an all-zero record (u = v = 0,
-// zero conic, o = 0: alpha = 0 at every pixel), which a row reads once its
-// list has ended.
+// Records the forward stages in LDS per batch, capacity of a quadrant's visit
+// list, and the LDS slot of an all-zero record (u = v = 0, zero conic, o = 0:
+// alpha = 0 at every pixel), which a row reads once its list has ended.
 constexpr int kFwdBatch = 448;
-constexpr int kBwdBatch = 512;
-constexpr int kQuadBatch = 256;
 constexpr int kListCap = 128;
 constexpr int kWavesPerTile = kTileThreads / kWave;
-static_assert(kFwdBatch % kWave == 0 && kBwdBatch % kWave == 0 && kQuadBatch % kWave == 0 && kListCap >= kWave,
+static_assert(kFwdBatch % kWave == 0 && kListCap % 4 == 0 && kListCap >= kWave,
               "batch / list shape");
 
 struct Block {
@@ -185,28 +174,18 @@ struct FwdSmem {
   uint16_t list[kWavesPerTile][4][kListCap + 4];
 };
 
-// Backward, block walk: the batch's records and their Gaussian ids.
-struct BwdSmem {
-  static constexpr int kBatch = kBwdBatch;
-  float4 uvab[kBatch];
-  float4 cob[kBatch];
-  float4 rgbz[kBatch];
-  uint32_t gid[kBatch];
-  int max_last;
-};
+// Where the backward's sums go: float or double atomics (see kWideSums), or
+// stored per (list position, block) for the deterministic option.
+enum BwdSums { kFloat, kWide, kStored };
 
-// Backward, quadrant walk (six fields): the batch's records (and the all-zero
-// record), their Gaussian ids, six per-Gaussian partial sums per record (zero
-// between batches) and one visit list per (wave, quadrant).
-struct QuadSmem {
-  static constexpr int kBatch = kQuadBatch, kDummy = kQuadBatch, kNF = 6;
-  float4 uvab[kBatch + 1];
-  float4 cob[kBatch + 1];
-  float4 rgbz[kBatch + 1];
-  float acc[kBatch * kNF];
-  uint32_t gid[kBatch];
-  uint16_t list[kWavesPerTile][4][kListCap + 4];
-  int max_last;
+// Backward: a wave's ring of records still to be walked (u, v, pa, pb | pc, o,
+// list position, Gaussian id | r, g, b, z). Up to three are left when the next
+// chunk of 64 is appended.
+constexpr int kRing = 128;
+struct BwdWave {
+  float4 uvab[kRing];
+  float4 copg[kRing];
+  float4 rgbz[kRing];
 };
 
 // The all-zero record; written once per workgroup before its first barrier.
@@ -363,65 +342,64 @@ __device__ __forceinline__ void fwd_item(const Raster& Rr, const FwdArgs& a, int
   }
 }
 
-// Quadrants of the block (bit k = quadrant k, row-major) where the record can
-// reach alpha >= alpha_min: its support box meets the quadrant and the
-// ellipse test passes on the quadrant itself.
-__device__ __forceinline__ uint32_t quad_mask_exact(const float4& g, const float4& cb, const Block& s,
-                                                    float log2_amin) {
-  const uint32_t bx = __float_as_uint(cb.z), by = __float_as_uint(cb.w);
-  const int x0 = (int)(bx & 0xffffu), x1 = (int)(bx >> 16), y0 = (int)(by & 0xffffu), y1 = (int)(by >> 16);
-  uint32_t m = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    Block qb;
-    qb.x0 = s.x0 + 4 * (k & 1);
-    qb.x1 = qb.x0 + 3;
-    qb.y0 = s.y0 + 4 * (k >> 1);
-    qb.y1 = qb.y0 + 3;
-    if ((x0 <= qb.x1) & (x1 >= qb.x0) & (y0 <= qb.y1) & (y1 >= qb.y0))
-      m |= ellipse_meets(g, cb, qb, log2_amin) ? (1u << k) : 0u;
-  }
-  return m;
+// The values of lane ^ 4 and lane ^ 8 (inside a 16-lane row).
+template <int CTRL>
+__device__ __forceinline__ float dpp_all(float v) {  // every lane has a source lane
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_xor4(float v) { return dpp_all<0x1b>(dpp_all<0x141>(v)); }  // half_mirror, quad_perm [3,2,1,0]
+__device__ __forceinline__ float row_xor8(float v) { return dpp_all<0x128>(v); }                 // row_ror:8
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// D_b[i][j] += A_b[i] B_b[j] for the wave's 16 blocks b of four lanes: A's row
+// i and B's column j lie in lane 4 b + i and 4 b + j, D's element (i, j) in
+// register i of lane 4 b + j. Each element is one fused multiply-add.
+__device__ __forceinline__ f32x4 outer4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
 }
 
-// Lanes whose bit is set in the wave-uniform mask m (c bits) append `val` to
-// `list` after its first `len` entries, highest lane first.
-__device__ __forceinline__ void list_append_desc(uint16_t* list, int len, uint64_t m, int c, int lane, int val) {
-  if ((m >> lane) & 1ull) {
-    const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    list[len + c - 1 - below] = (uint16_t)val;
-  }
-}
-
-// Maximum over the lane's 16-lane row.
-__device__ __forceinline__ int row_max_int(int v) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
-// Sums of six per-lane partials (fields 0-4 and 9, numbered 0-5) over each
-// 16-lane row. Field-splitting: at each exchange a lane keeps half of its
-// fields and hands the other half to its partner (row_mirror pairs lane bit
-// 3, row_half_mirror bit 2, quad_perm [2,3,0,1] bit 1), then the pair across
-// bit 0 is summed: lanes (b3 b2 b1 b0) with b0 = 0 and 2 b2 + b1 <= 2 end
-// with field 3 b3 + 2 b2 + b1. Returns the lane's sum and sets *f to its
-// field, or -1.
-__device__ __forceinline__ float row_reduce6(const float v[10], int lane, int* f) {
-  const bool b3 = (lane >> 3) & 1, b2 = (lane >> 2) & 1, b1 = (lane >> 1) & 1, b0 = lane & 1;
-  const float w6[6] = {v[0], v[1], v[2], v[3], v[4], v[9]};
-  float r[4];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) r[k] = (b3 ? w6[3 + k] : w6[k]) + dpp_f<0x140>(b3 ? w6[k] : w6[3 + k]);  // row_mirror
-  r[3] = 0.f;
-  float s[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) s[k] = (b2 ? r[2 + k] : r[k]) + dpp_f<0x141>(b2 ? r[k] : r[2 + k]);  // row_half_mirror
-  float t = (b1 ? s[1] : s[0]) + dpp_f<0x4e>(b1 ? s[0] : s[1]);  // quad_perm [2,3,0,1]
-  t += dpp_f<0xb1>(t);                                          // quad_perm [1,0,3,2]
-  const int loc = 2 * (int)b2 + (int)b1;
-  *f = (!b0 && loc <= 2) ? 3 * (int)b3 + loc : -1;
-  return t;
+// In every group of four lanes, the transpose of the 4x4 matrices a and b
+// (register s of lane i becomes register i of lane s): two exchanges of lane
+// pairs, each element one select whose one side comes from the partner lane.
+// A lane's values reach only their own places, whatever they hold (NaN and
+// infinities too). Written as one block because the select takes a partner
+// lane's value only with its mask in VCC; the waits are those that a DPP read
+// of a freshly written register needs (two) at the start and between the
+// exchanges, and that a matrix instruction's read needs at the end.
+__device__ __forceinline__ void transpose4(float a[4], float b[4], uint64_t even, uint64_t low) {
+  const uint64_t odd = ~even, high = ~low;
+  float p0, p1, p2, p3, q0, q1, q2, q3;
+#define GSR_SEL(d, x, y, perm) "v_cndmask_b32_dpp " d ", " x ", " y ", vcc quad_perm:" perm " row_mask:0xf bank_mask:0xf\n"
+  asm("s_mov_b64 vcc, %[ev]\n"
+      "s_nop 1\n"
+      GSR_SEL("%[p0]", "%[a1]", "%[a0]", "[1,0,3,2]")
+      GSR_SEL("%[p2]", "%[a3]", "%[a2]", "[1,0,3,2]")
+      GSR_SEL("%[q0]", "%[b1]", "%[b0]", "[1,0,3,2]")
+      GSR_SEL("%[q2]", "%[b3]", "%[b2]", "[1,0,3,2]")
+      "s_mov_b64 vcc, %[od]\n"
+      GSR_SEL("%[p1]", "%[a0]", "%[a1]", "[1,0,3,2]")
+      GSR_SEL("%[p3]", "%[a2]", "%[a3]", "[1,0,3,2]")
+      GSR_SEL("%[q1]", "%[b0]", "%[b1]", "[1,0,3,2]")
+      GSR_SEL("%[q3]", "%[b2]", "%[b3]", "[1,0,3,2]")
+      "s_mov_b64 vcc, %[lo]\n"
+      "s_nop 1\n"
+      GSR_SEL("%[a0]", "%[p2]", "%[p0]", "[2,3,0,1]")
+      GSR_SEL("%[a1]", "%[p3]", "%[p1]", "[2,3,0,1]")
+      GSR_SEL("%[b0]", "%[q2]", "%[q0]", "[2,3,0,1]")
+      GSR_SEL("%[b1]", "%[q3]", "%[q1]", "[2,3,0,1]")
+      "s_mov_b64 vcc, %[hi]\n"
+      GSR_SEL("%[a2]", "%[p0]", "%[p2]", "[2,3,0,1]")
+      GSR_SEL("%[a3]", "%[p1]", "%[p3]", "[2,3,0,1]")
+      GSR_SEL("%[b2]", "%[q0]", "%[q2]", "[2,3,0,1]")
+      GSR_SEL("%[b3]", "%[q1]", "%[q3]", "[2,3,0,1]")
+      "s_nop 1"
+      : [a0] "+v"(a[0]), [a1] "+v"(a[1]), [a2] "+v"(a[2]), [a3] "+v"(a[3]), [b0] "+v"(b[0]), [b1] "+v"(b[1]),
+        [b2] "+v"(b[2]), [b3] "+v"(b[3]), [p0] "=&v"(p0), [p1] "=&v"(p1), [p2] "=&v"(p2), [p3] "=&v"(p3),
+        [q0] "=&v"(q0), [q1] "=&v"(q1), [q2] "=&v"(q2), [q3] "=&v"(q3)
+      : [ev] "s"(even), [od] "s"(odd), [lo] "s"(low), [hi] "s"(high)
+      : "vcc");
+#undef GSR_SEL
 }
 
 // Column of the [n, 10] gradient sums that field f of the six-field
@@ -431,7 +409,7 @@ __device__ __forceinline__ int g2d_field6(int f) { return f < 5 ? f : 9; }
 // Per-pixel state of the backward: the forward's final transmittance and last
 // composited position, the upstream gradients, and the running suffix term.
 struct BwdPix {
-  float T, g0, g1, g2, gd, gS, gA;
+  float T, g0, g1, g2, gd, gS;
   int last;
 };
 
@@ -440,7 +418,7 @@ struct BwdPix {
 // sum_{u > j} z_u alpha_u T_u (depth), g = (gC, gD). Only the dot product
 // gS = g . S_j is needed; the background enters it through T_fin bg.
 __device__ __forceinline__ BwdPix bwd_pixel(const Raster& Rr, const BwdArgs& a, const Pixel& q) {
-  BwdPix b{1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0};
+  BwdPix b{1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0};
   float ga = 0.f;
   if (q.inside) {
     const int64_t P = (int64_t)Rr.W * Rr.H;
@@ -454,304 +432,218 @@ __device__ __forceinline__ BwdPix bwd_pixel(const Raster& Rr, const BwdArgs& a, 
     b.gd = a.gD[p];
     ga = a.gA ? a.gA[p] : 0.f;
   }
-  b.gS = b.T * (b.g0 * Rr.bg0 + b.g1 * Rr.bg1 + b.g2 * Rr.bg2);
-  b.gA = ga * b.T;
+  b.gS = b.T * (b.g0 * Rr.bg0 + b.g1 * Rr.bg1 + b.g2 * Rr.bg2) - ga * b.T;
   return b;
 }
 
-// One pair of the back-to-front walk: recomputes T_j, advances the suffix
-// term and writes the ten per-pair partials (sums of q (dx, dy, dx^2, dx dy,
-// dy^2) with q = dL/dp / ln 2 for alpha = o 2^p, then d alpha / d o times
-// dL/dalpha, colour, direct depth). A lane without a hit runs the same
-// instructions with alpha = 0: its transmittance and suffix term are
-// unchanged and its partials are 0.
-__device__ __forceinline__ void bwd_pair(BwdPix& b, const PairEval& pe, bool hit, float dx, float dy,
-                                         const float4& cz, float v[10]) {
-  const float al = hit ? pe.alpha : 0.f;
-  const float inv = __builtin_amdgcn_rcpf(1.f - al);  // 1 ulp; alpha <= alpha_max < 1
-  const float Tj = b.T * inv;
-  const float wt = al * Tj;
-  v[6] = wt * b.g0;
-  v[7] = wt * b.g1;
-  v[8] = wt * b.g2;
-  v[9] = wt * b.gd;
-  const float gc = fmaf(b.g0, cz.x, fmaf(b.g1, cz.y, fmaf(b.g2, cz.z, b.gd * cz.w)));
-  const float dA = fmaf(Tj, gc, -inv * (b.gS - b.gA));
-  b.gS = fmaf(gc, wt, b.gS);
-  b.T = Tj;
-  // a clamped alpha does not depend on o or sigma
-  const float dAs = (hit && !pe.clamped) ? dA : 0.f;
-  v[5] = dAs * pe.e;  // d alpha / d o = exp(-sigma)
-  // the projection backward turns the sums of q (dx, dy, dx^2, dx dy, dy^2)
-  // into dL/d(u, v) and the conic terms
-  const float gp = dAs * pe.alpha;
-  const float gpx = gp * dx, gpy = gp * dy;
-  v[0] = gpx;
-  v[1] = gpy;
-  v[2] = gpx * dx;
-  v[3] = gpx * dy;
-  v[4] = gpy * dy;
-}
-
-// Backward of one item, block walk (all ten fields: mapping). Each wave walks
-// the records that can reach its 8x8 block (support box, then the ellipse
-// test) back to front from the largest `last` of its pixels, one record per
-// step with the record broadcast from LDS; a wave's sums of a record's ten
-// partials come from a field-splitting butterfly and go to the [n, 10]
-// gradient sums with one 10-lane atomic (DET: they are stored at (list
-// position, wave) of a.part, and the wave's bit set in a.mask).
-template <bool DET>
-__device__ __forceinline__ void bwd_item_block(const Raster& Rr, const BwdArgs& a, int item, BwdSmem& sm) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const Pixel q = item_pixel(Rr, item);
-  BwdPix b = bwd_pixel(Rr, a, q);
-  __syncthreads();  // the previous item (persistent launch) is done with max_last
-  if (tid == 0) sm.max_last = 0;
-  __syncthreads();
-  if (b.last > 0) atomicMax(&sm.max_last, b.last);
-  const int wmax = wave_max_int(b.last);
-  __syncthreads();
-  const int bmax = sm.max_last;
-  const int start = a.ranges[item].x;
-
-  constexpr int kBatch = BwdSmem::kBatch;
-  for (int bend = start + bmax; bend > start; bend -= kBatch) {
-    const int bstart = max(start, bend - kBatch);
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < (kBatch + kTileThreads - 1) / kTileThreads; ++h) {
-      const int sl = h * kTileThreads + tid, i = bstart + sl;
-      if (sl < kBatch && i < bend) {
-        const uint32_t gid = a.ids[i];
-        sm.gid[sl] = gid;
-        sm.uvab[sl] = a.rec_uvab[kRec * gid];
-        sm.cob[sl] = a.rec_cob[kRec * gid];
-        sm.rgbz[sl] = a.rec_rgbz[kRec * gid];
-      }
-    }
-    __syncthreads();
-    const int cnt = min(bend, start + wmax) - bstart;  // records this wave may need
-    for (int c = (cnt - 1) >> 6; c >= 0; --c) {
-      const int r = c * kWave + lane;
-      bool meets = false;
-      if (r < cnt) {
-        const float4 cb = sm.cob[r];
-        meets = block_meets(sm.uvab[r], cb, q.blk, Rr.log2_amin);
-      }
-      uint64_t m = __ballot(meets);
-      const int cbase = __builtin_amdgcn_readfirstlane(c * kWave);  // keep the index arithmetic scalar
-      // one visit: the record at slot li (its three float4s already in registers)
-      auto visit = [&](const float4& g, const float4& cb, const float4& cz, int li) {
-        const int pos = bstart + li - start;
-        const float dx = q.fpx - g.x, dy = q.fpy - g.y;
-        const PairEval pe = eval_pair(dx, dy, g.z, g.w, cb.x, cb.y, Rr.amin, Rr.amax);
-        const bool hit = pos < b.last && pe.use;
-        if (!__any(hit)) return;
-        float v[10];
-        bwd_pair(b, pe, hit, dx, dy, cz, v);
-        int f;
-        const float u = wave_reduce10(v, lane, &f);
-        if (DET) {
-          const int64_t slot = bstart + li;  // position in the ids array
-          if (f >= 0) a.part[(slot * 16 + w) * 10 + f] = u;
-          if (lane == 0) atomicOr(a.mask + slot, 1u << w);
-        } else if (f >= 0) {
-          atomicAdd(a.g2d + 10 * (int64_t)sm.gid[li] + f, u);
-        }
-      };
-      // the highest remaining record of the mask (removed from it)
-      auto take = [&]() {
-        const int bit = 63 - __builtin_clzll(m);
-        m &= ~(1ull << bit);
-        return cbase + bit;
-      };
-      // Software pipeline, unrolled by two: the next visit's record is read
-      // from LDS while the current one is evaluated, into the other register
-      // set, so no record is copied between registers.
-      if (m == 0) continue;
-      int lA = take();
-      float4 gA = sm.uvab[lA], cbA = sm.cob[lA], czA = sm.rgbz[lA];
-      for (;;) {
-        const bool moreB = m != 0;
-        int lB = 0;
-        float4 gB, cbB, czB;
-        if (moreB) {
-          lB = take();
-          gB = sm.uvab[lB];
-          cbB = sm.cob[lB];
-          czB = sm.rgbz[lB];
-        }
-        visit(gA, cbA, czA, lA);
-        if (!moreB) break;
-        const bool moreA = m != 0;
-        if (moreA) {
-          lA = take();
-          gA = sm.uvab[lA];
-          cbA = sm.cob[lA];
-          czA = sm.rgbz[lA];
-        }
-        visit(gB, cbB, czB, lB);
-        if (!moreA) break;
-      }
-    }
-  }
-}
-
-// Backward of one item, quadrant walk (the six fields of a pose-only
-// backward: tracking). Each wave walks its 8x8 block back to front from the
-// largest `last` of its pixels; per batch of records staged in LDS, each of
-// its four rows (4x4 quadrants) gets a visit list of the records that can
-// reach alpha >= alpha_min in the quadrant (support box and ellipse test on
-// the quadrant) at a position before the quadrant's largest `last`, in
-// descending position; the rows walk their lists side by side, a row whose
-// list has ended reading the all-zero record. A row's sums of a record's six
-// partials are added to the record's accumulator in LDS; after the batch the
-// workgroup adds every non-zero accumulator to the [n, 10] gradient sums (one
-// global atomic per (Gaussian, tile, field)). On the 640 x 480 tracking frame
-// this beats the block walk (smaller Gaussians on screen leave more of a
-// block's quadrants untouched); with ten fields on the 1200 x 680 mapping
-// frame the block walk is faster (its lists are hardly longer than the
-// quadrants', and its butterfly serves 64 lanes per record).
+// Backward of one wave's 8x8 block (block w of the item's tile), with NF = 10
+// fields (mapping) or 6 (a pose-only backward). The wave reads the records of
+// the tile's list in chunks of 64 from the largest `last` of its pixels
+// downwards, appends those that can reach alpha >= alpha_min in its block
+// (support box, then the ellipse test) to a ring in LDS, and walks the ring
+// four records per step, each lane its own pixel.
 //
-// DET: instead of the LDS accumulators, each row stores its sums of a record
-// to a.part at (list position of the record, quadrant of the tile) and sets
-// that quadrant's bit in a.mask; a later pass adds them per Gaussian in a
-// fixed order, so the result does not depend on the order rows and
-// workgroups run in.
-template <bool DET>
-__device__ __forceinline__ void bwd_item_quad(const Raster& Rr, const BwdArgs& a, int item, QuadSmem& sm) {
-  constexpr int kBatch = QuadSmem::kBatch, kDummy = QuadSmem::kDummy, NF = QuadSmem::kNF;
+// The sums over the block's pixels are contractions and run on the matrix
+// cores, in FP32 (4x4x1 outer products, exact fused multiply-adds). With q =
+// dL/dp / ln 2 and wt = alpha T of the step's four records:
+//  - g . c (upstream gradient dot colour and depth) of four records: four
+//    outer products of the records' channels with the pixels' gradients;
+//  - q and wt are transposed inside each group of four lanes, so that a lane
+//    holds one record's values at the group's four pixels, which lie in one
+//    pixel row;
+//  - the group's sums of q (1, X, X^2), X = x about the group's centre, and
+//    of wt (g_r, g_g, g_b, g_d): outer products with per-pixel columns that
+//    are constant for the item. As y is constant in the group, the six
+//    moments about the record's centre follow with a few operations.
+// The 16 groups are then added by exchanges that split the fields over the
+// lanes, and one 40-lane atomic adds the four records' fields to the [n, 10]
+// gradient sums. The sum over q alone is o dL/do (the projection backward
+// divides by the opacity).
+//
+// Bound by VALU issue (about 0.9 while a CU is busy): some 200 issue slots per
+// step of four records, where DPP sums of every pair's ten products and one
+// 64-lane butterfly per record took about 80 per record. A matrix instruction
+// takes two slots, so those are used where one replaces more than two
+// operations; the transposes as outer products with unit vectors (180 us) and
+// the pixel offsets as outer products (no change) are not.
+// Measured at 1200x680 with 500K Gaussians / 640x480 with 500K, six fields:
+// 267 / 146 us before (there a block walk, here one of per-quadrant lists with
+// LDS accumulators, both with workgroup batches and barriers), 175 / 118 us
+// now. On the way: the same sums with workgroup batches of 512 records 198 /
+// 149 us; visit lists per 4x4 quadrant (0.6 of the steps, but sums per
+// quadrant) with LDS float atomics 330 / 158 us, as those take about two
+// cycles per lane, with global atomics 1.1 ms / 344 us, as they need several
+// times the cache lines of atomic traffic.
+//
+// kStored: the wave's sums of a record are stored to a.part at (list position of
+// the record, block of the tile) and the block's bit set in a.mask instead; a
+// later pass adds them per Gaussian in a fixed order, so the result does not
+// depend on the order waves run in.
+template <int NF, BwdSums SUMS>
+__device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, int item, BwdWave* smem) {
+  constexpr int H = NF / 2;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const Pixel q = item_pixel(Rr, item);
   BwdPix b = bwd_pixel(Rr, a, q);
-  __syncthreads();  // the previous item (persistent launch) is done with max_last
-  if (tid == 0) sm.max_last = 0;
-  __syncthreads();
-  if (b.last > 0) atomicMax(&sm.max_last, b.last);
-  // the largest `last` of each quadrant (row), wave-uniform
-  const int rl = row_max_int(b.last);
-  const int ql0 = __builtin_amdgcn_readlane(rl, 0), ql1 = __builtin_amdgcn_readlane(rl, 16);
-  const int ql2 = __builtin_amdgcn_readlane(rl, 32), ql3 = __builtin_amdgcn_readlane(rl, 48);
-  const int wmax = max(max(ql0, ql1), max(ql2, ql3));
-  __syncthreads();
-  const int bmax = sm.max_last;
-  const int start = a.ranges[item].x;
-  const uint16_t* mylist = sm.list[w][q.quad];
-
-  for (int bend = start + bmax; bend > start; bend -= kBatch) {
-    const int bstart = max(start, bend - kBatch);
-    const int boff = bstart - start;  // list position of slot 0
-    __syncthreads();  // the previous batch's flush is done with gid and acc
+  // per-lane constants of the outer products: lane 4 b + i holds, for pixel s
+  // of block b, row i of (1, X, X^2, 0) and of the upstream gradients
+  const int li = lane & 3;
+  const bool b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1;
+  // the field a lane's sum ends with (see the reduction below), or -1
+  const int b54 = ((lane >> 5) & 1) + 2 * ((lane >> 4) & 1);
+  const int fld0 = NF == 10 ? (b2 ? 8 + b54 : 4 * (int)b3 + b54) : 4 * (int)b3 + b54;
+  const int fld = NF == 10 ? ((b2 && (b3 || b54 > 1)) ? -1 : fld0) : ((b2 || fld0 > 5) ? -1 : fld0);
+  float phi[4], G[4];
 #pragma unroll
-    for (int h = 0; h < (kBatch + kTileThreads - 1) / kTileThreads; ++h) {
-      const int sl = h * kTileThreads + tid, i = bstart + sl;
-      if (sl < kBatch && i < bend) {
-        const uint32_t gid = a.ids[i];
-        sm.gid[sl] = gid;
-        sm.uvab[sl] = a.rec_uvab[kRec * gid];
-        sm.cob[sl] = a.rec_cob[kRec * gid];
-        sm.rgbz[sl] = a.rec_rgbz[kRec * gid];
-      }
-    }
-    __syncthreads();
-    const int cnt = min(bend, start + wmax) - bstart;  // records this wave may need
-    int k = cnt > 0 ? (cnt - 1) >> 6 : -1;
-    while (k >= 0) {
-      // one segment: append chunks (back to front) to the quadrant lists until one would overflow
-      int len0 = 0, len1 = 0, len2 = 0, len3 = 0;
-      for (; k >= 0; --k) {
-        const int r = k * kWave + lane;
-        const int pos = boff + r;
-        const uint32_t qm = r < cnt ? quad_mask_exact(sm.uvab[r], sm.cob[r], q.blk, Rr.log2_amin) : 0u;
-        const uint64_t m0 = __ballot((qm & 1u) && pos < ql0);
-        const uint64_t m1 = __ballot((qm & 2u) && pos < ql1);
-        const uint64_t m2 = __ballot((qm & 4u) && pos < ql2);
-        const uint64_t m3 = __ballot((qm & 8u) && pos < ql3);
-        const int c0 = __popcll(m0), c1 = __popcll(m1), c2 = __popcll(m2), c3 = __popcll(m3);
-        if (len0 + c0 > kListCap || len1 + c1 > kListCap || len2 + c2 > kListCap || len3 + c3 > kListCap) break;
-        // entries are LDS byte offsets of the slot inside each record array
-        list_append_desc(sm.list[w][0], len0, m0, c0, lane, 16 * r);
-        list_append_desc(sm.list[w][1], len1, m1, c1, lane, 16 * r);
-        list_append_desc(sm.list[w][2], len2, m2, c2, lane, 16 * r);
-        list_append_desc(sm.list[w][3], len3, m3, c3, lane, 16 * r);
-        len0 += c0;
-        len1 += c1;
-        len2 += c2;
-        len3 += c3;
-      }
-      const int myl = q.quad == 0 ? len0 : (q.quad == 1 ? len1 : (q.quad == 2 ? len2 : len3));
-      const int maxl = __builtin_amdgcn_readfirstlane(max(max(len0, len1), max(len2, len3)));
-      __builtin_amdgcn_wave_barrier();
-      // one step per record of the row's list (pend: the row's list has not ended)
-      auto step = [&](const float4& g, const float4& cb, const float4& cz, int jb, bool pend) {
-        const float dx = q.fpx - g.x, dy = q.fpy - g.y;
-        const PairEval pe = eval_pair(dx, dy, g.z, g.w, cb.x, cb.y, Rr.amin, Rr.amax);
-        const bool hit = boff + (jb >> 4) < b.last && pe.use;  // the all-zero record never passes `use`
-        float v[10];
-        bwd_pair(b, pe, hit, dx, dy, cz, v);
-        int f;
-        const float u = row_reduce6(v, lane, &f);
-        if (DET) {
-          if (__ballot(hit) != 0) {
-            const int64_t slot = bstart + (jb >> 4);  // position in the ids array
-            const int quad = 4 * w + q.quad;          // quadrant of the tile
-            if (pend && f >= 0) a.part[(slot * 16 + quad) * NF + f] = u;
-            if (pend && (lane & 15) == 0) atomicOr(a.mask + slot, 1u << quad);
-          }
-        } else if (pend && f >= 0) {
-          atomicAdd(sm.acc + NF * (jb >> 4) + f, u);
-        }
-      };
-      // Software pipeline, unrolled by two so that no record is copied
-      // between registers: while step t runs on one record set, the other
-      // set receives the record of step t + 1 from LDS, and the list entry of
-      // step t + 2 is read (entries past the row's list end are not used).
-      // The loop is tested at its end only, so with an odd maxl its last
-      // step runs past every row's list: a no-op (the all-zero record, no
-      // accumulation), and entries up to kListCap + 2 exist for its reads.
-      int jA = 0 < myl ? mylist[0] : 16 * kDummy;
-      int jn = mylist[1];
-      float4 gA = lds_at(sm.uvab, jA), cbA = lds_at(sm.cob, jA), czA = lds_at(sm.rgbz, jA);
-      if (0 < maxl) {
-        int t = 0;
-        do {
-          const int jB = t + 1 < myl ? jn : 16 * kDummy;
-          jn = mylist[t + 2];
-          const float4 gB = lds_at(sm.uvab, jB), cbB = lds_at(sm.cob, jB), czB = lds_at(sm.rgbz, jB);
-          step(gA, cbA, czA, jA, t < myl);
-          ++t;
-          jA = t + 1 < myl ? jn : 16 * kDummy;
-          jn = mylist[t + 2];
-          gA = lds_at(sm.uvab, jA);
-          cbA = lds_at(sm.cob, jA);
-          czA = lds_at(sm.rgbz, jA);
-          step(gB, cbB, czB, jB, t < myl);
-          ++t;
-        } while (t < maxl);
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
-    if (DET) continue;
-    __syncthreads();  // every row's sums of this batch are in acc
-    for (int i = tid; i < (bend - bstart) * NF; i += kTileThreads) {
-      const float val = sm.acc[i];
-      if (val != 0.f) {
-        const int slot = i / NF, f = i - slot * NF;
-        atomicAdd(a.g2d + 10 * (int64_t)sm.gid[slot] + g2d_field6(f), val);
-        sm.acc[i] = 0.f;
-      }
-    }
+  for (int s = 0; s < 4; ++s) {
+    const float X = (float)s - 1.5f;
+    phi[s] = li == 0 ? 1.f : (li == 1 ? X : (li == 2 ? X * X : 0.f));
   }
-}
+#define GSR_GRAD_ROW(s, ctrl)                                                                                    \
+  {                                                                                                      \
+    const float t0 = dpp_f<ctrl>(b.g0), t1 = dpp_f<ctrl>(b.g1), t2 = dpp_f<ctrl>(b.g2), t3 = dpp_f<ctrl>(b.gd); \
+    G[s] = li == 0 ? t0 : (li == 1 ? t1 : (li == 2 ? t2 : t3));                                          \
+  }
+  GSR_GRAD_ROW(0, 0x00)
+  GSR_GRAD_ROW(1, 0x55)
+  GSR_GRAD_ROW(2, 0xaa)
+  GSR_GRAD_ROW(3, 0xff)
+#undef GSR_GRAD_ROW
+  const float xc = (float)(q.blk.x0 + 4 * (q.quad & 1)) + 1.5f;  // the centre of the lane's block of four pixels
+  const int start = a.ranges[item].x;
+  const int wmax = __builtin_amdgcn_readfirstlane(wave_max_int(b.last));
+  BwdWave& sm = smem[w];
 
-// The all-zero record and zero accumulators; written before the first barrier.
-__device__ __forceinline__ void init_smem(QuadSmem& sm) {
-  if (threadIdx.x == 0) {
-    sm.uvab[QuadSmem::kDummy] = make_float4(0.f, 0.f, 0.f, 0.f);
-    sm.cob[QuadSmem::kDummy] = make_float4(0.f, 0.f, 0.f, 0.f);
-    sm.rgbz[QuadSmem::kDummy] = make_float4(0.f, 0.f, 0.f, 0.f);
+  // Records come in chunks of 64, the highest positions first: lane l reads
+  // the record at position pos0 - l, tests it, and appends it to the ring if
+  // it can reach the block. The next chunk's records are read while the
+  // current ones are walked.
+  uint32_t gid = 0;
+  float4 uvab = make_float4(0.f, 0.f, 0.f, 0.f), cob = uvab, rgbz = uvab;
+  auto fetch = [&](int pos0) {
+    const int pos = pos0 - lane;
+    if (pos >= 0) {
+      gid = a.ids[start + pos];
+      uvab = a.rec_uvab[kRec * gid];
+      cob = a.rec_cob[kRec * gid];
+      rgbz = a.rec_rgbz[kRec * gid];
+    }
+  };
+  fetch(wmax - 1);
+  int head = 0, tail = 0;
+  for (int pos0 = wmax - 1; pos0 >= 0; pos0 -= kWave) {
+    const bool meets = pos0 - lane >= 0 && block_meets(uvab, cob, q.blk, Rr.log2_amin);
+    const uint64_t m = __ballot(meets);
+    if (meets) {
+      const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      const int sl = (tail + below) & (kRing - 1);
+      sm.uvab[sl] = uvab;
+      sm.copg[sl] = make_float4(cob.x, cob.y, __int_as_float(pos0 - lane), __uint_as_float(gid));
+      sm.rgbz[sl] = rgbz;
+    }
+    tail += __popcll(m);
+    if (pos0 < kWave) {
+      // no more records: all-zero ones (alpha = 0) fill the last step
+      if (lane < 3) {
+        const int sl = (tail + lane) & (kRing - 1);
+        sm.uvab[sl] = make_float4(0.f, 0.f, 0.f, 0.f);
+        sm.copg[sl] = make_float4(0.f, 0.f, __int_as_float(-1), 0.f);
+        sm.rgbz[sl] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      tail += 3;
+    }
+    fetch(pos0 - kWave);
+    __builtin_amdgcn_wave_barrier();
+    for (; tail - head >= 4; head += 4) {
+      const int h = head & (kRing - 1);
+      float4 g[4], co[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        g[s] = sm.uvab[h + s];
+        co[s] = sm.copg[h + s];
+      }
+      const float4 cz = sm.rgbz[h + li], mine = sm.copg[h + li];  // the record this lane sums
+      const float2 uv = *reinterpret_cast<const float2*>(&sm.uvab[h + li]);  // its centre
+      f32x4 gc = {0.f, 0.f, 0.f, 0.f}, M = gc, Wm = gc;
+      float qT[4], wT[4];
+      gc = outer4(cz.w, b.gd, gc);
+      gc = outer4(cz.z, b.g2, gc);
+      gc = outer4(cz.y, b.g1, gc);
+      gc = outer4(cz.x, b.g0, gc);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const float dx = q.fpx - g[s].x, dy = q.fpy - g[s].y;
+        const PairEval pe = eval_pair(dx, dy, g[s].z, g[s].w, co[s].x, co[s].y, Rr.amin, Rr.amax);
+        const bool hit = (__float_as_int(co[s].z) < b.last) & pe.use;  // the all-zero record never passes `use`
+        // A lane without a hit runs the same instructions with alpha = 0: its
+        // transmittance and suffix term are unchanged, q and wt are 0.
+        const float al = hit ? pe.alpha : 0.f;
+        const float inv = __builtin_amdgcn_rcpf(1.f - al);  // 1 ulp; alpha <= alpha_max < 1
+        const float Tj = b.T * inv;
+        const float wt = al * Tj;
+        const float dA = fmaf(Tj, gc[s], -inv * b.gS);
+        b.gS = fmaf(gc[s], wt, b.gS);
+        b.T = Tj;
+        // a clamped alpha does not depend on o or sigma
+        const float gp = (hit & !pe.clamped) ? dA * pe.alpha : 0.f;
+        qT[s] = gp;
+        wT[s] = wt;
+      }
+      transpose4(qT, wT, 0x5555555555555555ull, 0x3333333333333333ull);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        M = outer4(phi[s], qT[s], M);
+        Wm = outer4(G[s], wT[s], Wm);
+      }
+      // moments about the record's centre (u, v): x = X - U, y = dy
+      const float U = uv.x - xc, dy = q.fpy - uv.y;
+      const float mx = fmaf(-U, M[0], M[1]);
+      const float mxx = fmaf(-U, M[1] + mx, M[2]);
+      const float my = dy * M[0], mxy = dy * mx, myy = dy * my;
+      float v[NF];
+      v[0] = mx;
+      v[1] = my;
+      v[2] = mxx;
+      v[3] = mxy;
+      v[4] = myy;
+      if (NF == 10) {
+        v[5] = M[0];
+        v[NF - 4] = Wm[0];
+        v[NF - 3] = Wm[1];
+        v[NF - 2] = Wm[2];
+      }
+      v[NF - 1] = Wm[3];
+      // The wave's sum over its 16 blocks, the fields split over the lanes'
+      // bits 5 .. 2: one field (or none) per lane and record is left.
+      float r5[H], r4[(H + 1) / 2];
+#pragma unroll
+      for (int f = 0; f < H; ++f) r5[f] = perm_add32(v[2 * f], v[2 * f + 1]);
+#pragma unroll
+      for (int f = 0; f < (H + 1) / 2; ++f) r4[f] = perm_add16(r5[2 * f], 2 * f + 1 < H ? r5[2 * f + 1] : 0.f);
+      float o;
+      if (NF == 10) {
+        const float a0 = (b3 ? r4[1] : r4[0]) + row_xor8(b3 ? r4[0] : r4[1]);
+        const float a1 = r4[2] + row_xor8(r4[2]);
+        o = (b2 ? a1 : a0) + row_xor4(b2 ? a0 : a1);
+      } else {
+        const float a0 = (b3 ? r4[1] : r4[0]) + row_xor8(b3 ? r4[0] : r4[1]);
+        o = a0 + row_xor4(a0);
+      }
+      const int pos = __float_as_int(mine.z);
+      if (fld >= 0 && pos >= 0) {
+        if (SUMS == kStored) {
+          const int64_t slot = start + pos;  // position in the ids array
+          a.part[(slot * 4 + w) * NF + fld] = o;
+          if (fld == 0) atomicOr(a.mask + slot, 1u << w);
+        } else {
+          const int64_t at = 10 * (int64_t)__float_as_uint(mine.w) + (NF == 10 ? fld : g2d_field6(fld));
+          if (SUMS == kWide) atomicAdd(reinterpret_cast<double*>(a.g2d) + at, (double)o);
+          else atomicAdd(a.g2d + at, o);
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
   }
-  for (int i = threadIdx.x; i < QuadSmem::kBatch * QuadSmem::kNF; i += kTileThreads) sm.acc[i] = 0.f;
 }
 
 template <bool STATS>
@@ -761,17 +653,10 @@ __global__ __launch_bounds__(kTileThreads) void k_render_fwd(Raster Rr, FwdArgs 
   fwd_item<STATS>(Rr, a, xcd_tile(blockIdx.x, gridDim.x), sm);
 }
 
-template <bool DET>
-__global__ __launch_bounds__(kTileThreads) void k_render_bwd_block(Raster Rr, BwdArgs a) {
-  __shared__ BwdSmem sm;
-  bwd_item_block<DET>(Rr, a, xcd_tile(blockIdx.x, gridDim.x), sm);
-}
-
-template <bool DET>
-__global__ __launch_bounds__(kTileThreads) void k_render_bwd_quad(Raster Rr, BwdArgs a) {
-  __shared__ QuadSmem sm;
-  init_smem(sm);
-  bwd_item_quad<DET>(Rr, a, xcd_tile(blockIdx.x, gridDim.x), sm);
+template <int NF, BwdSums SUMS>
+__global__ __launch_bounds__(kTileThreads, 5) void k_render_bwd(Raster Rr, BwdArgs a) {
+  __shared__ BwdWave sm[kWavesPerTile];
+  bwd_item<NF, SUMS>(Rr, a, xcd_chunk((int)blockIdx.x, (int)gridDim.x), sm);
 }
 
 // Persistent workgroups: take the next item from the queue until it is empty.
@@ -796,26 +681,14 @@ __global__ __launch_bounds__(kTileThreads) void k_render_fwd_persistent(Raster R
   }
 }
 
-template <bool DET>
-__global__ __launch_bounds__(kTileThreads) void k_render_bwd_block_persistent(Raster Rr, BwdArgs a) {
-  __shared__ BwdSmem sm;
+template <int NF, BwdSums SUMS>
+__global__ __launch_bounds__(kTileThreads, 5) void k_render_bwd_persistent(Raster Rr, BwdArgs a) {
+  __shared__ BwdWave sm[kWavesPerTile];
   __shared__ int s_item;
   for (;;) {
     const int item = next_item(a.queue, a.order, a.n_items, &s_item);
     if (item < 0) break;
-    bwd_item_block<DET>(Rr, a, item, sm);
-  }
-}
-
-template <bool DET>
-__global__ __launch_bounds__(kTileThreads) void k_render_bwd_quad_persistent(Raster Rr, BwdArgs a) {
-  __shared__ QuadSmem sm;
-  __shared__ int s_item;
-  init_smem(sm);
-  for (;;) {
-    const int item = next_item(a.queue, a.order, a.n_items, &s_item);
-    if (item < 0) break;
-    bwd_item_quad<DET>(Rr, a, item, sm);
+    bwd_item<NF, SUMS>(Rr, a, item, sm);
   }
 }
 
@@ -838,8 +711,8 @@ __global__ __launch_bounds__(256) void k_det_rev(Raster Rr, const int2* __restri
 }
 
 // Deterministic backward, after the compositing pass: one thread per (record,
-// field) adds the stored quadrant sums of its tiles (tiles in row-major order
-// of the record's rectangle, quadrants in order) and stores the total into
+// field) adds the stored block sums of its tiles (tiles in row-major order
+// of the record's rectangle, blocks in order) and stores the total into
 // the [n, 10] gradient sums.
 template <int NF>
 __global__ __launch_bounds__(256) void k_det_reduce(const int4* __restrict__ rect, const uint32_t* __restrict__ goff,
@@ -858,9 +731,9 @@ __global__ __launch_bounds__(256) void k_det_reduce(const int4* __restrict__ rec
     const int64_t slot = rev[b + j];
     uint32_t m = mask[slot];
     while (m) {
-      const int quad = __builtin_ctz(m);
+      const int blk = __builtin_ctz(m);
       m &= m - 1u;
-      sum += part[(slot * 16 + quad) * NF + f];
+      sum += part[(slot * 4 + blk) * NF + f];
     }
   }
   g2d[10 * o + (NF == 10 ? f : g2d_field6(f))] = sum;
@@ -961,26 +834,22 @@ void launch_render_fwd(const Raster& R, const FwdArgs& a, hipStream_t s) {
 void launch_render_bwd(const Raster& R, const BwdArgs& a, hipStream_t s) {
   const dim3 tb(kTileThreads);
   const bool det = a.part != nullptr;
-  // ten fields: block walk; the six of a pose-only backward: quadrant walk
-  if (a.blocks > 0) {
-    launch_fill_u32(reinterpret_cast<uint32_t*>(a.queue), 0u, 1, s);
-    const dim3 grid((unsigned)a.blocks);
-    if (a.geom_only) {
-      if (det) hipLaunchKernelGGL(k_render_bwd_quad_persistent<true>, grid, tb, 0, s, R, a);
-      else hipLaunchKernelGGL(k_render_bwd_quad_persistent<false>, grid, tb, 0, s, R, a);
-    } else {
-      if (det) hipLaunchKernelGGL(k_render_bwd_block_persistent<true>, grid, tb, 0, s, R, a);
-      else hipLaunchKernelGGL(k_render_bwd_block_persistent<false>, grid, tb, 0, s, R, a);
-    }
+  const bool queue = a.blocks > 0;
+  const dim3 grid((unsigned)(queue ? a.blocks : a.n_items));
+  if (queue) launch_fill_u32(reinterpret_cast<uint32_t*>(a.queue), 0u, 1, s);
+  auto go = [&](auto one, auto many) {
+    if (queue) hipLaunchKernelGGL(many, grid, tb, 0, s, R, a);
+    else hipLaunchKernelGGL(one, grid, tb, 0, s, R, a);
+  };
+  // ten fields, or the six of a pose-only backward
+  if (a.geom_only) {
+    if (det) go(k_render_bwd<6, kStored>, k_render_bwd_persistent<6, kStored>);
+    else if (a.wide) go(k_render_bwd<6, kWide>, k_render_bwd_persistent<6, kWide>);
+    else go(k_render_bwd<6, kFloat>, k_render_bwd_persistent<6, kFloat>);
   } else {
-    const dim3 grid((unsigned)a.n_items);
-    if (a.geom_only) {
-      if (det) hipLaunchKernelGGL(k_render_bwd_quad<true>, grid, tb, 0, s, R, a);
-      else hipLaunchKernelGGL(k_render_bwd_quad<false>, grid, tb, 0, s, R, a);
-    } else {
-      if (det) hipLaunchKernelGGL(k_render_bwd_block<true>, grid, tb, 0, s, R, a);
-      else hipLaunchKernelGGL(k_render_bwd_block<false>, grid, tb, 0, s, R, a);
-    }
+    if (det) go(k_render_bwd<10, kStored>, k_render_bwd_persistent<10, kStored>);
+    else if (a.wide) go(k_render_bwd<10, kWide>, k_render_bwd_persistent<10, kWide>);
+    else go(k_render_bwd<10, kFloat>, k_render_bwd_persistent<10, kFloat>);
   }
 }
 

@@ -1,0 +1,82 @@
+"""The backward's walk over a block's records: list lengths around its steps of
+four and its chunks of 64, both widths of the gradient sums, and what a
+non-finite upstream gradient reaches. Bars as in test_gpu_parity."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2312_10070_amd import gsr
+from tests import gpu_cases as G
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+CAM = oracle.Camera(19, 11, 20.0, 20.0, 9.0, 5.0, 0.2, (0.1, 0.2, 0.3))  # ragged: two tiles, cut blocks
+POSE = np.array([1, 0, 0, 0, 0, 0, 0], np.float64)
+
+
+def stack(m, n, seed):
+    """m Gaussians over the image at well separated depths (opacities low enough that no pixel stops early),
+    the other n - m behind the camera."""
+    rng = np.random.default_rng(seed)
+    z = 1.0 + 0.03 * np.arange(n)
+    g = dict(means=np.stack([rng.uniform(-0.3, 0.3, n) * z, rng.uniform(-0.2, 0.2, n) * z, z], 1),
+             scales=rng.uniform(0.05, 0.2, (n, 3)) * z[:, None], quats=rng.normal(size=(n, 4)),
+             opacities=rng.uniform(0.02, 0.05, n), colors=rng.uniform(0, 1, (n, 3)))
+    g["means"][m:, 2] = -1.0
+    return G.certify(g, POSE, CAM, 1e-4) if n <= 1000 else G.f32(g)
+
+
+def backward(g, gC, gD, **kw):
+    import torch
+    d = G.to_dev(g)
+    camera = gsr.make_camera(CAM.width, CAM.height, CAM.fx, CAM.fy, CAM.cx, CAM.cy, CAM.near_z, CAM.bg)
+    pose = torch.tensor(POSE.astype(np.float32), device="cuda")
+    _, _, _, st = gsr.render_fwd(d["means"], d["scales"], d["quats"], d["opacities"], d["colors"], pose, camera)
+    out = gsr.render_bwd(st, torch.from_numpy(gC).cuda(), torch.from_numpy(gD).cuda(), None, **kw)
+    torch.cuda.synchronize()
+    st.release()
+    return {k: v.cpu().numpy() for k, v in out.items()}
+
+
+@pytest.mark.parametrize("m", [1, 3, 4, 5, 63, 64, 65, 67, 68, 129])
+@pytest.mark.parametrize("n", [None, 40000])  # n <= 32768: sums in double, above: in float
+def test_walk_lengths(m, n):
+    g = stack(m, m if n is None else n, m)
+    rng = np.random.default_rng(m + 1)
+    gC = rng.normal(size=(3, CAM.height, CAM.width)).astype(np.float32)
+    gD = rng.normal(size=(CAM.height, CAM.width)).astype(np.float32)
+    vis = {k: v[:m] for k, v in g.items()}
+    ref = oracle.backward(vis, POSE, CAM, oracle.Opts(amb_z=0.0), gC, gD)
+    full = backward(g, gC, gD)
+    if n is not None:
+        assert all(not np.any(full[k][m:]) for k in gsr.PARAM_GROUPS)
+    G.grads_check({k: full[k][:m] for k in gsr.PARAM_GROUPS}, ref, case=f"walk {m}")
+    pose_only = backward(g, gC, gD, want_params=False)
+    for out in (full, pose_only):
+        for k in ("pose7", "twist6"):
+            H.check_grad_ref(k, out[k], ref, case=f"walk {m}")
+
+
+def test_non_finite_upstream_stays_in_its_pixel():
+    """A NaN upstream gradient at one pixel: the geometry of records of the same step of the walk that do not
+    cover the pixel is not touched by it, and blocks without the pixel not at all."""
+    n = 8
+    g = dict(means=np.zeros((n, 3)), scales=np.full((n, 3), 0.02), quats=np.tile([1.0, 0, 0, 0], (n, 1)),
+             opacities=np.full(n, 0.3), colors=np.full((n, 3), 0.5))
+    z = 1.0 + 0.05 * np.arange(n)
+    # alternately around pixel (2, 2), around pixel (6, 6) of the same block, and in another block
+    px = np.array([2, 6, 2, 6, 13, 6, 2, 13], np.float64)
+    py = np.array([2, 6, 2, 6, 3, 6, 2, 3], np.float64)
+    g["means"] = np.stack([(px - CAM.cx) / CAM.fx * z, (py - CAM.cy) / CAM.fy * z, z], 1)
+    g["scales"] = np.full((n, 3), 0.02)
+    gC = np.full((3, CAM.height, CAM.width), 0.5, np.float32)
+    gD = np.full((CAM.height, CAM.width), 0.25, np.float32)
+    want = backward(G.f32(g), gC, gD, want_pose=False)
+    gC[1, 2, 2] = np.nan
+    got = backward(G.f32(g), gC, gD, want_pose=False)
+    clean = px != 2
+    assert np.isnan(got["means"][~clean]).all()
+    for k in ("means", "scales", "quats", "opacities"):
+        np.testing.assert_array_equal(got[k][clean], want[k][clean], err_msg=k)
+    np.testing.assert_array_equal(got["colors"][px == 13], want["colors"][px == 13])
