@@ -1155,6 +1155,21 @@ int gsr_autotune_batch(gsr_ctx* c, const gsr_gaussians* g, int32_t n_views, cons
 // Tracking-initialisation network
 // ---------------------------------------------------------------------------
 
+namespace {
+// The BF16 working copies of the weights, made wherever the FP32 masters change.
+void cast_weights(gsr_initnet* net, hipStream_t st) {
+  gsr::CastWeights a{};
+  a.n = gsr_initnet::kLayers;
+  for (int l = 0; l < a.n; ++l) {
+    a.C[l] = net->C[l];
+    a.w[l] = net->w[l];
+    a.wk[l] = net->wk[l];
+    a.wt[l] = net->wt[l];
+  }
+  gsr::launch_cast_weights(a, st);
+}
+}  // namespace
+
 int gsr_initnet_destroy(gsr_ctx* c, gsr_initnet* net) {
   if (!c || !net || net->ctx != c) return fail(c, GSR_EINVAL, "invalid network");
   (void)hipSetDevice(c->device);
@@ -1232,6 +1247,7 @@ int gsr_initnet_create(gsr_ctx* c, int32_t max_batch, gsr_initnet** out) {
   net->bfc = p + 6 * N::kHeadIn;
   net->dbfc = g + 6 * N::kHeadIn;
   for (float* q : {net->params, net->grads, net->m, net->v}) gsr::launch_fill_f32(q, 0.f, np, c->stream);
+  cast_weights(net, c->stream);
   *out = net;
   return check_launch(c, "gsr_initnet_create");
 }
@@ -1249,6 +1265,7 @@ int gsr_initnet_set_params(gsr_ctx* c, gsr_initnet* net, const float* src) {
   gsr::launch_fill_f32(net->m, 0.f, net->n_params, c->stream);
   gsr::launch_fill_f32(net->v, 0.f, net->n_params, c->stream);
   net->step = 0;
+  cast_weights(net, c->stream);
   return check_launch(c, "gsr_initnet_set_params");
 }
 
@@ -1300,7 +1317,6 @@ int gsr_initnet_forward(gsr_ctx* c, gsr_initnet* net, int32_t batch, float* out)
   hipStream_t st = c->stream;
   Stage t(c, "initnet_fwd");
   for (int l = 0; l < gsr_initnet::kLayers; ++l) {
-    gsr::launch_cast_weights(net->w[l], net->C[l], net->wk[l], net->wt[l], st);
     gsr::launch_conv_fwd(batch, net->H[l], net->W[l], net->C[l], net->act[l], net->wk[l], net->b[l], net->act[l + 1],
                          st);
   }
@@ -1329,8 +1345,8 @@ int gsr_initnet_backward(gsr_ctx* c, gsr_initnet* net, int32_t batch, const floa
     gsr::launch_conv_bwd_weight(batch, net->H[l], net->W[l], net->C[l], net->dact[l + 1], net->act[l], net->dw[l],
                                 net->db[l], st);
     if (l > 0)
-      gsr::launch_conv_bwd_data(batch, net->H[l], net->W[l], net->C[l], net->dact[l + 1], net->wt[l], net->act[l],
-                                net->dact[l], st);
+      gsr::launch_conv_bwd_data(batch, net->H[l], net->W[l], net->dact[l + 1], net->wt[l], net->act[l], net->dact[l],
+                                st);
   }
   return check_launch(c, "gsr_initnet_backward");
 }
@@ -1342,6 +1358,7 @@ int gsr_initnet_adam(gsr_ctx* c, gsr_initnet* net, float lr, float b1, float b2,
   const float bc1 = (float)(1.0 - std::pow((double)b1, (double)net->step));
   const float bc2 = (float)(1.0 - std::pow((double)b2, (double)net->step));
   gsr::launch_adam(net->params, net->m, net->v, net->grads, net->n_params, lr, b1, b2, eps, bc1, bc2, c->stream);
+  cast_weights(net, c->stream);
   return check_launch(c, "gsr_initnet_adam");
 }
 
