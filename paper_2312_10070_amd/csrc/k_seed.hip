@@ -17,9 +17,11 @@
 // the cell edge h is r_max (1 + 1e-3), so every mean within r_max of a query
 // lies in the 27 cells around the query's cell, whatever the rounding of the
 // cell index (cell coordinates below 8192 in magnitude keep that rounding
-// under 1e-3 of a cell). The squared distance (dx^2 + dy^2) + dz^2 is evaluated without
-// contraction, and the minimum is exact, so results do not depend on the
-// order in which the grid is filled.
+// under 1e-3 of a cell). Buckets of neighbouring cells along x lie side by
+// side (blocks of eight are hashed), so the three cells of a row are one range
+// of the means, or two where they straddle blocks. The squared distance
+// (dx^2 + dy^2) + dz^2 is evaluated without contraction, and the minimum is
+// exact, so results do not depend on the order in which the grid is filled.
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -30,9 +32,12 @@ __device__ __forceinline__ int cell_of(float x, float inv_h) {
   return (int)floorf(fminf(fmaxf(x * inv_h, -1.0e9f), 1.0e9f));
 }
 
+constexpr int kRowLog2 = 3, kRow = 1 << kRowLog2;  // cells of a hashed block, along x
+
+// mask = number of hashed blocks - 1
 __device__ __forceinline__ uint32_t bucket_of(int cx, int cy, int cz, uint32_t mask) {
-  const uint32_t h = (uint32_t)cx * 73856093u ^ (uint32_t)cy * 19349663u ^ (uint32_t)cz * 83492791u;
-  return (h ^ (h >> 15)) & mask;
+  const uint32_t h = (uint32_t)(cx >> kRowLog2) * 73856093u ^ (uint32_t)cy * 19349663u ^ (uint32_t)cz * 83492791u;
+  return ((h ^ (h >> 15)) & mask) * kRow + (uint32_t)(cx & (kRow - 1));
 }
 
 __device__ __forceinline__ float dist2(float ax, float ay, float az, float bx, float by, float bz) {
@@ -41,69 +46,121 @@ __device__ __forceinline__ float dist2(float ax, float ay, float az, float bx, f
   return (dx * dx + dy * dy) + dz * dz;
 }
 
+// counts: zero on entry. rank[i] = how many means reached bucket i's before
+// mean i: with it the fill needs no second round of atomics, whose rate (about
+// 17 G/s on scattered addresses) bounds this kernel.
 __global__ __launch_bounds__(256) void k_grid_count(const float* __restrict__ p, int64_t n, float inv_h,
-                                                  uint32_t mask, uint32_t* __restrict__ counts) {
+                                                  uint32_t mask, uint32_t* __restrict__ counts,
+                                                  uint32_t* __restrict__ rank) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const uint32_t b = bucket_of(cell_of(p[3 * i], inv_h), cell_of(p[3 * i + 1], inv_h), cell_of(p[3 * i + 2], inv_h),
                                mask);
-  atomicAdd(&counts[b], 1u);
+  rank[i] = atomicAdd(&counts[b], 1u);
 }
 
-// cursor: zero on entry; pts[offsets[b] + k] = the k-th mean that reached bucket b
+// pts[offsets[b] + k] = the k-th mean that reached bucket b (500,000 means:
+// 33 -> 12 us against a cursor advanced with atomics)
 __global__ __launch_bounds__(256) void k_grid_fill(const float* __restrict__ p, int64_t n, float inv_h, uint32_t mask,
-                                                 const uint32_t* __restrict__ offsets, uint32_t* __restrict__ cursor,
-                                                 float4* __restrict__ pts) {
+                                                 const uint32_t* __restrict__ offsets,
+                                                 const uint32_t* __restrict__ rank, float4* __restrict__ pts) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const float x = p[3 * i], y = p[3 * i + 1], z = p[3 * i + 2];
   const uint32_t b = bucket_of(cell_of(x, inv_h), cell_of(y, inv_h), cell_of(z, inv_h), mask);
-  const uint32_t slot = offsets[b] + atomicAdd(&cursor[b], 1u);
-  pts[slot] = make_float4(x, y, z, 0.f);
+  pts[offsets[b] + rank[i]] = make_float4(x, y, z, 0.f);
 }
 
-// offsets: T + 1 words, bucket b's means are pts[offsets[b], offsets[b + 1]).
-// Workgroups are dealt to the 8 XCDs in turn; xcd_tile gives each XCD a
-// contiguous run of queries (candidates come in pixel order, so a run covers a
-// band of the image and its XCD's L2 holds the part of the grid it needs).
-__global__ __launch_bounds__(256) void k_seed_query(const float* __restrict__ q, int64_t m, float inv_h, uint32_t mask,
-                                                  const uint32_t* __restrict__ offsets,
+// Lower bounds of the squared distances, along one axis, from a query to the
+// cells on the lower and on the upper side of its own; f = its position in the
+// cell, v = its coordinate in cells. The rounding of the query's and of a
+// mean's cell index is 2^-24 of the coordinate each: 2^-22 of it and 2e-3 of a
+// cell are taken off, and 1e-5 relative for the rounding of the squares and
+// their sum.
+__device__ __forceinline__ float side2(float f, float v, int d, float h) {
+  const float g = fmaxf((d < 0 ? f : 1.f - f) - (2e-3f + fabsf(v) * 0x1p-22f), 0.f) * h;
+  return d == 0 ? 0.f : g * g * (1.f - 1e-5f);
+}
+
+// Lanes per query and means that each of them reads per step.
+constexpr uint32_t kLanes = 4, kStep = 8;
+
+// The minimum over a query's four lanes.
+__device__ __forceinline__ float lanes_min(float v) {
+  v = fminf(v, dpp_f<0xb1>(v));  // quad_perm [1,0,3,2]
+  return fminf(v, dpp_f<0x4e>(v));  // quad_perm [2,3,0,1]
+}
+
+// offsets: buckets + 1 words, bucket b's means are pts[offsets[b], offsets[b + 1]).
+// Rows of three cells along x, the query's own first; a row, or a cell at its
+// ends, that begins farther away than the best so far is skipped, which leaves
+// the minimum exact.
+// Workgroups are dealt to the 8 XCDs in chunks, so that each XCD's L2 holds a
+// few bands of the image's candidates and the dense bands are shared out.
+// Bound by the latency of divergent loads, two offsets and then the means of
+// each range, one after the other: hence several lanes per query and eight
+// independent loads a lane. 579,000 queries against 500,000 means, few with a
+// neighbour in reach: 773 us with a lane per query walking 27 buckets; rows of
+// three with a lane per query 437, with lanes x means per step 4 x 2 294,
+// 4 x 4 234, 4 x 8 225, 8 x 2 264, 8 x 4 224, 16 x 1 370, 16 x 2 298. The same
+// where most have one: 620, and 4 x 4 157, 4 x 8 138, 8 x 4 177.
+__global__ __launch_bounds__(256) void k_seed_query(const float* __restrict__ q, int64_t m, float inv_h, float h,
+                                                  uint32_t mask, const uint32_t* __restrict__ offsets,
                                                   const float4* __restrict__ pts, float r2max, float rho2,
                                                   float* __restrict__ nn_d2, int32_t* __restrict__ keep) {
-  const int64_t j = (int64_t)xcd_tile((int)blockIdx.x, (int)gridDim.x) * blockDim.x + threadIdx.x;
+  const int64_t j = ((int64_t)xcd_chunk((int)blockIdx.x, (int)gridDim.x) * blockDim.x + threadIdx.x) / kLanes;
   if (j >= m) return;
+  const uint32_t sub = threadIdx.x % kLanes;
   const float x = q[3 * j], y = q[3 * j + 1], z = q[3 * j + 2];
   const int cx = cell_of(x, inv_h), cy = cell_of(y, inv_h), cz = cell_of(z, inv_h);
+  const float fx = x * inv_h - (float)cx, fy = y * inv_h - (float)cy, fz = z * inv_h - (float)cz;
+  const float xlo = side2(fx, x * inv_h, -1, h), xhi = side2(fx, x * inv_h, 1, h);
   float best = r2max;
-  // a 3x3 slice of cells at a time: its nine bucket ranges are loaded
-  // together, then each bucket's means four per step, so that several loads
-  // are in flight (a step past a bucket's end repeats its first mean of the
-  // step; the minimum is exact, so neither that nor the order matters)
-  for (int dz = -1; dz <= 1; ++dz) {
-    uint32_t s[9], e[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const uint32_t b = bucket_of(cx + t % 3 - 1, cy + t / 3 - 1, cz + dz, mask);
-      s[t] = offsets[b];
-      e[t] = offsets[b + 1];
-    }
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const uint32_t end = e[t];
-      for (uint32_t k = s[t]; k < end; k += 4) {
-        const float4 p0 = pts[k];
-        const float4 p1 = pts[k + 1 < end ? k + 1 : k];
-        const float4 p2 = pts[k + 2 < end ? k + 2 : k];
-        const float4 p3 = pts[k + 3 < end ? k + 3 : k];
-        best = fminf(best, dist2(x, y, z, p0.x, p0.y, p0.z));
-        best = fminf(best, dist2(x, y, z, p1.x, p1.y, p1.z));
-        best = fminf(best, dist2(x, y, z, p2.x, p2.y, p2.z));
-        best = fminf(best, dist2(x, y, z, p3.x, p3.y, p3.z));
+  // The lanes of a query walk its ranges (a row's part in the first cell's
+  // block, then its part in the next block; the rows from the own outwards)
+  // with one loop over steps, so the wave runs as long as its longest query
+  // and not as the sum of the longest ranges.
+  uint32_t k = 0, end = 0, k2 = 0, end2 = 0;
+  int row = -1;
+  for (;;) {
+    while (k >= end) {  // next range
+      if (k2 < end2) {
+        k = k2;
+        end = end2;
+        end2 = 0;
+        break;
+      }
+      if (++row >= 9) break;
+      const int o = (int)(0x862075314ull >> (4 * row)) & 15;  // own, faces, edges
+      const int dy = o % 3 - 1, dz = o / 3 - 1;
+      const float low = side2(fy, y * inv_h, dy, h) + side2(fz, z * inv_h, dz, h);
+      if (low >= best) continue;
+      // the row's cells that begin near enough
+      const int c0 = low + xlo < best ? cx - 1 : cx, c1 = low + xhi < best ? cx + 1 : cx;
+      const uint32_t b0 = bucket_of(c0, cy + dy, cz + dz, mask), b1 = bucket_of(c1, cy + dy, cz + dz, mask);
+      const bool one = (c0 >> kRowLog2) == (c1 >> kRowLog2);
+      k = offsets[b0];
+      end = offsets[(one ? b1 : b0 | (kRow - 1)) + 1];
+      if (!one) {
+        k2 = offsets[b1 & ~(uint32_t)(kRow - 1)];
+        end2 = offsets[b1 + 1];
       }
     }
+    if (row >= 9) break;
+    // (an index past the end repeats the range's last mean; the minimum is
+    // exact, so neither that nor the order matters)
+    float4 p[kStep];
+#pragma unroll
+    for (uint32_t u = 0; u < kStep; ++u) p[u] = pts[min(k + kLanes * u + sub, end - 1)];
+#pragma unroll
+    for (uint32_t u = 0; u < kStep; ++u) best = fminf(best, dist2(x, y, z, p[u].x, p[u].y, p[u].z));
+    k += kLanes * kStep;
+    best = lanes_min(best);
   }
-  if (nn_d2) nn_d2[j] = best;
-  if (keep) keep[j] = best < rho2 ? 0 : 1;
+  if (sub == 0) {
+    if (nn_d2) nn_d2[j] = best;
+    if (keep) keep[j] = best < rho2 ? 0 : 1;
+  }
 }
 
 __device__ __forceinline__ float grey(const float* C, int64_t P, int64_t i) {
@@ -234,10 +291,11 @@ uint32_t seed_buckets(int64_t n) {
   return t;
 }
 
-// words before the float4 point array, rounded up to 16 bytes
-static int64_t seed_pts_offset(int64_t T) { return (3 * T + 1 + scan_temp_words(T) + 3) & ~(int64_t)3; }
+// counts [T] | offsets [T + 1] | scan temp | ranks [n] | points [n] float4, 16-byte aligned
+static int64_t seed_rank_offset(int64_t T) { return 2 * T + 1 + scan_temp_words(T); }
+static int64_t seed_pts_offset(int64_t T, int64_t n) { return (seed_rank_offset(T) + n + 3) & ~(int64_t)3; }
 
-int64_t seed_temp_words(int64_t n) { return seed_pts_offset(seed_buckets(n)) + 4 * n; }
+int64_t seed_temp_words(int64_t n) { return seed_pts_offset(seed_buckets(n), n) + 4 * n; }
 
 // the cell edge h = r_max (1 + 1e-3) as its reciprocal
 static float seed_inv_h(float r_max) { return (float)(1.0 / ((double)r_max * 1.001)); }
@@ -245,31 +303,30 @@ static float seed_inv_h(float r_max) { return (float)(1.0 / ((double)r_max * 1.0
 void launch_seed_grid(const float* means, int64_t n, float r_max, uint32_t* temp, hipStream_t s) {
   const uint32_t T = seed_buckets(n);
   uint32_t* counts = temp;
-  uint32_t* cursor = temp + T;
-  uint32_t* offsets = temp + 2 * (int64_t)T;
+  uint32_t* offsets = temp + T;
   uint32_t* total = offsets + T;  // offsets[T] = n
   uint32_t* scan_tmp = total + 1;
-  float4* pts = reinterpret_cast<float4*>(temp + seed_pts_offset(T));
+  uint32_t* rank = temp + seed_rank_offset(T);
+  float4* pts = reinterpret_cast<float4*>(temp + seed_pts_offset(T, n));
   const float inv_h = seed_inv_h(r_max);
-  const uint32_t mask = T - 1;
+  const uint32_t mask = T / kRow - 1;
   launch_fill_u32(counts, 0u, T, s);
-  launch_fill_u32(cursor, 0u, T, s);
   const unsigned gn = (unsigned)((n + 255) / 256);
-  if (n > 0) hipLaunchKernelGGL(k_grid_count, dim3(gn), dim3(256), 0, s, means, n, inv_h, mask, counts);
+  if (n > 0) hipLaunchKernelGGL(k_grid_count, dim3(gn), dim3(256), 0, s, means, n, inv_h, mask, counts, rank);
   launch_exclusive_scan(counts, offsets, T, total, scan_tmp, s);
-  if (n > 0) hipLaunchKernelGGL(k_grid_fill, dim3(gn), dim3(256), 0, s, means, n, inv_h, mask, offsets, cursor, pts);
+  if (n > 0) hipLaunchKernelGGL(k_grid_fill, dim3(gn), dim3(256), 0, s, means, n, inv_h, mask, offsets, rank, pts);
 }
 
 void launch_seed_query(int64_t n, const float* points, int64_t m, float rho, float r_max, float* nn_d2,
                        int32_t* keep, const uint32_t* temp, hipStream_t s) {
   const uint32_t T = seed_buckets(n);
-  const uint32_t* offsets = temp + 2 * (int64_t)T;
-  const float4* pts = reinterpret_cast<const float4*>(temp + seed_pts_offset(T));
+  const uint32_t* offsets = temp + T;
+  const float4* pts = reinterpret_cast<const float4*>(temp + seed_pts_offset(T, n));
   const float r2max = r_max * r_max, rho2 = rho * rho;
-  const unsigned gm = (unsigned)((m + 255) / 256);
+  const unsigned gm = (unsigned)((m * kLanes + 255) / 256);
   if (m > 0)
-    hipLaunchKernelGGL(k_seed_query, dim3(gm), dim3(256), 0, s, points, m, seed_inv_h(r_max), T - 1, offsets, pts,
-                       r2max, rho2, nn_d2, keep);
+    hipLaunchKernelGGL(k_seed_query, dim3(gm), dim3(256), 0, s, points, m, seed_inv_h(r_max),
+                       (float)((double)r_max * 1.001), T / kRow - 1, offsets, pts, r2max, rho2, nn_d2, keep);
 }
 
 }  // namespace gsr

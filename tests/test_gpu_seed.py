@@ -86,6 +86,34 @@ def test_seed_query_cell_boundaries(offset):
     assert (nn_ref < cap).any() and (nn_ref == cap).any()
 
 
+@pytest.mark.parametrize("base", [0, 7, -1, 130_000])
+@pytest.mark.parametrize("per", [1, 31, 33, 70])
+def test_seed_query_rows_and_blocks(base, per):
+    """per means in each cell of a 4^3 block of cells that straddles a border of
+    the hashed blocks of eight cells along x, and queries all over it. The
+    result is never above the FP32 minimum over the 27 cells around the query
+    and never below the minimum over all means; the two are equal, and the
+    result exact, unless the coordinate's own rounding exceeds the margin."""
+    r_max, rho = np.float32(0.25), 0.05
+    inv_h = np.float32(1.0 / (float(r_max) * 1.001))
+    rng = np.random.default_rng(per)
+    k = np.stack(np.meshgrid(*[np.arange(-2, 2)] * 3, indexing="ij"), -1).reshape(-1, 3) + np.array([base + 1, 0, 3])
+    p = ((np.repeat(k, per, 0) + rng.uniform(0, 1, (64 * per, 3))) * (float(r_max) * 1.001)).astype(np.float32)
+    q = ((k[rng.integers(0, 64, 1500)] + rng.uniform(-1, 2, (1500, 3))) * (float(r_max) * 1.001)).astype(np.float32)
+    cell = lambda a: np.floor(a * inv_h).astype(np.int64)
+    d = q[:, None, :] - p[None]
+    d2 = (d[..., 0] * d[..., 0] + d[..., 1] * d[..., 1]) + d[..., 2] * d[..., 2]
+    near = (np.abs(cell(q)[:, None, :] - cell(p)[None]) <= 1).all(-1)
+    r2 = r_max * r_max
+    lo = np.minimum(d2.min(1), r2)
+    hi = np.minimum(np.where(near, d2, np.float32(np.inf)).min(1), r2)
+    nn, keep = run(p, q, rho, float(r_max))
+    assert (nn >= lo).all() and (nn <= hi).all()
+    if base < 8192:
+        np.testing.assert_array_equal(lo, hi)
+    np.testing.assert_array_equal(keep, np.where(nn < np.float32(rho) * np.float32(rho), 0, 1))
+
+
 def test_seed_query_bad_arguments():
     torch = torch_()
     p = dev(np.zeros((4, 3)))
