@@ -323,10 +323,15 @@ void launch_seed_query(int64_t n, const float* points, int64_t m, float rho, flo
   const uint32_t* offsets = temp + T;
   const float4* pts = reinterpret_cast<const float4*>(temp + seed_pts_offset(T, n));
   const float r2max = r_max * r_max, rho2 = rho * rho;
-  const unsigned gm = (unsigned)((m * kLanes + 255) / 256);
-  if (m > 0)
-    hipLaunchKernelGGL(k_seed_query, dim3(gm), dim3(256), 0, s, points, m, seed_inv_h(r_max),
-                       (float)((double)r_max * 1.001), T / kRow - 1, offsets, pts, r2max, rho2, nn_d2, keep);
+  // a launch holds fewer than 2^32 threads
+  constexpr int64_t kSlice = int64_t(1) << 29;
+  for (int64_t j = 0; j < m; j += kSlice) {
+    const int64_t mj = m - j < kSlice ? m - j : kSlice;
+    const unsigned gm = (unsigned)((mj * kLanes + 255) / 256);
+    hipLaunchKernelGGL(k_seed_query, dim3(gm), dim3(256), 0, s, points + 3 * j, mj, seed_inv_h(r_max),
+                       (float)((double)r_max * 1.001), T / kRow - 1, offsets, pts, r2max, rho2,
+                       nn_d2 ? nn_d2 + j : nullptr, keep ? keep + j : nullptr);
+  }
 }
 
 }  // namespace gsr
