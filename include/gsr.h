@@ -25,6 +25,9 @@
  *    transform x_cam = R(q/|q|) mu + t. Camera axes: +x right, +y down, +z
  *    forward; pixel (px,py) is sampled at the continuous point (px,py).
  *  - Images are planar: color [3,H,W], depth [H,W], alpha [H,W].
+ *  - "Temporary device memory" of the seeding and pruning calls is kept by the
+ *    context for the next such call: two allocations of at most 256 MiB, freed
+ *    by gsr_ctx_destroy; what exceeds them is freed before the call returns.
  *  - Every call enqueues work on the context's HIP stream and returns without
  *    waiting, except where noted ("synchronises"). Inputs must stay alive and
  *    unmodified until the stream has passed the call; the backward re-reads
@@ -216,7 +219,7 @@ int gsr_loss_l1(gsr_ctx *ctx, const float *color, const float *depth, const floa
  * and X_w = R^T (X_c - t) for the world-to-camera pose7 (device, q normalised
  * inside). points and colors (device float [W H, 3] capacity) receive the
  * chosen ones in row-major pixel order; *n_out (host) their count. color
- * [3,H,W], depth [H,W]; camera by pointer as for rendering. Allocates
+ * [3,H,W], depth [H,W]; camera by pointer as for rendering. Takes
  * temporary device memory and synchronises the context's stream. */
 int gsr_seed_candidates(gsr_ctx *ctx, const gsr_camera *cam, const float *pose7, const float *color,
                         const float *depth, const float *alpha, const float *u, float p_uniform, float p_grad,
@@ -284,7 +287,7 @@ int gsr_seed_query(gsr_ctx *ctx, const float *means, int64_t n, const float *poi
  * room for m rows, not aliased with the inputs (append new Gaussians by
  * passing pointers just past a sub-map's last row). *n_new (host) receives the
  * count. 0 <= m < 2^31 (m = 0: *n_new = 0, the arrays are not read).
- * Allocates temporary device memory and synchronises the context's stream.
+ * Takes temporary device memory and synchronises the context's stream.
  * GSR_EINVAL for NULL arrays (m > 0) or a misaligned quaternion output. */
 int gsr_seed_gaussians(gsr_ctx *ctx, int64_t m, const float *points, const float *colors, const float *nn_d2,
                        const int32_t *keep, float *const *out, int64_t *n_new);
@@ -298,7 +301,7 @@ int gsr_seed_gaussians(gsr_ctx *ctx, int64_t m, const float *points, const float
  * in[5..9] and in[10..14] = the matching Adam exp_avg / exp_avg_sq tensors,
  * each entry NULL if absent (out[t] must be NULL exactly where in[t] is).
  * Outputs are device buffers of the inputs' shapes (n rows), not aliased with
- * any input. *n_kept (host) receives the count. Allocates temporary device
+ * any input. *n_kept (host) receives the count. Takes temporary device
  * memory and synchronises the context's stream. 0 <= n < 2^31. */
 int gsr_prune(gsr_ctx *ctx, int64_t n, float o_thre, const float *const *in, float *const *out, int64_t *n_kept);
 

@@ -108,3 +108,45 @@ def test_submap_trigger_matches_oracle():
         assert got == oracle.submap_trigger(a.astype(np.float64), b.astype(np.float64), 0.5, np.deg2rad(50.0))
         hits += got
     assert 0 < hits < 400
+
+
+def test_kept_scratch_serves_other_sizes_threads_and_streams():
+    """Calls of changing sizes one after the other, and from four threads on
+    streams of their own (more than the context keeps scratch for): each gives
+    what the oracle gives."""
+    import threading
+    torch = torch_()
+    rng = np.random.default_rng(5)
+    jobs = []
+    for n in (4000, 300, 9000, 1):
+        g = groups(n, n)
+        p = rng.uniform(-1, 1, (n, 3)).astype(np.float32)
+        q = rng.uniform(-1, 1, (700, 3)).astype(np.float32)
+        dev = [{k: torch.from_numpy(v).cuda() for k, v in d.items()} for d in g]
+        jobs.append((dev, oracle.prune(g, 0.3), torch.from_numpy(p).cuda(), torch.from_numpy(q).cuda(),
+                     oracle.seed_query(p, q, 0.05, 0.2)))
+    torch.cuda.synchronize()
+    failures = []
+
+    def work(order):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for i in order:
+                    dev, (m_ref, ref), p, q, (nn_ref, keep_ref) = jobs[i]
+                    m, got, _, _ = gsr.prune(dev[0], 0.3)
+                    nn, keep = gsr.seed_query(p, q, 0.05, 0.2)
+                    torch.cuda.synchronize()
+                    assert m == m_ref
+                    np.testing.assert_array_equal(got["means"].cpu().numpy(), ref[0]["means"])
+                    np.testing.assert_array_equal(nn.cpu().numpy(), nn_ref)
+                    np.testing.assert_array_equal(keep.cpu().numpy(), keep_ref)
+        except BaseException as e:  # noqa: BLE001 - reported by the main thread
+            failures.append(e)
+
+    work([0, 1, 2, 3, 2, 0])
+    threads = [threading.Thread(target=work, args=([i, 3 - i, (i + 2) % 4] * 3,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failures, failures[0]
