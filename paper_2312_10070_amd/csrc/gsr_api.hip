@@ -45,7 +45,6 @@ struct gsr_state {
   float* pose_acc = nullptr;  // [views][projection-backward workgroups][12]
   int* queue = nullptr;       // persistent-launch work counter
   int* order = nullptr;       // [views * tiles] longest-list-first item order
-  int* order_temp = nullptr;  // 64 ints
   int n_views = 1;
   int blocks = 0;             // persistent workgroups (0 = one per item)
   // arena B: per overlap
@@ -200,7 +199,6 @@ void carve_A(gsr_state* s, char* base, int64_t n, int64_t P, int64_t tiles, int6
   s->pose_acc = c.take<float>(12 * (gsr::project_bwd_blocks(n) + views + 1));
   s->queue = c.take<int>(4);
   s->order = c.take<int>(tiles);
-  s->order_temp = c.take<int>(64);
   *bytes = c.off;
 }
 
@@ -465,7 +463,7 @@ struct Stage {
 
 gsr::BinArgs bin_args(gsr_state* s, int64_t cap, uint32_t* K_host = nullptr) {
   return gsr::BinArgs{s->n,     s->n_views, s->n_wg, s->rect, s->bin_M,    s->bin_T,       s->bin_R,
-                      s->bin_ticket, s->d_K, K_host, cap, s->keys, s->d_overflow};
+                      s->order, s->bin_ticket, s->d_K, K_host, cap, s->keys, s->d_overflow};
 }
 
 // Projection, per-(tile, workgroup) pair counts, the tiles' ranges and the
@@ -493,11 +491,10 @@ void enqueue_back(gsr_ctx* c, gsr_state* s, hipStream_t st, int64_t cap, float* 
   {
     Stage t(c, "tile_bins");
     gsr::launch_tile_bins(R, bin_args(s, cap), n_items, s->ranges, s->scratch, s->ids, st);
-    if (s->blocks > 0) gsr::launch_item_order(s->ranges, n_items, s->order, s->order_temp, st);
   }
   gsr::FwdArgs fa{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz,
                   color, depth, alpha, s->Tfin, s->last, nullptr,
-                  n_items, s->queue, s->blocks > 0 ? s->order : nullptr, s->blocks};
+                  n_items, s->queue, s->order, s->blocks};
   {
     Stage t(c, "render_fwd");
     gsr::launch_render_fwd(R, fa, st);
@@ -516,7 +513,7 @@ void enqueue_bwd(gsr_ctx* c, gsr_state* s, hipStream_t st, const float* gC, cons
   const bool geom_only = !adam && (!grads || (!grads->opacities && !grads->colors));
   const bool wide = !s->det && s->n * s->n_views <= gsr::kWideSums;
   gsr::BwdArgs ba{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz, s->Tfin, s->last,
-                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, s->blocks > 0 ? s->order : nullptr, s->blocks,
+                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, s->order, s->blocks,
                   nullptr, nullptr};
   if (s->det) {
     // arena D is in place (ensure_D): list positions of every (record, tile),
@@ -1495,7 +1492,7 @@ int gsr_state_stats(gsr_ctx* c, gsr_state* s, int64_t out[6]) {
   GSR_HIP(c, hipMemsetAsync(c->d_stats, 0, 64, st));
   gsr::FwdArgs fa{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz,
                   nullptr, nullptr, nullptr, nullptr, s->last, c->d_stats,
-                  s->R.n_tiles * s->n_views, nullptr, nullptr, 0};
+                  s->R.n_tiles * s->n_views, nullptr, s->order, 0};
   gsr::launch_render_fwd(s->R, fa, st);
   unsigned long long h[3] = {0, 0, 0};
   GSR_HIP(c, hipMemcpyAsync(h, c->d_stats, sizeof(h), hipMemcpyDeviceToHost, st));

@@ -67,21 +67,10 @@ __device__ __forceinline__ PairEval eval_pair(float dx, float dy, float pa, floa
   return r;
 }
 
-// Tile index of a workgroup. Workgroups are dealt round-robin to the 8 XCDs
-// (each with its own L2); this gives each XCD a contiguous run of row-major
-// tiles so neighbouring tiles, which share most Gaussians, hit the same L2.
-__device__ __forceinline__ int xcd_tile(int b, int nb) {
-  const int q = nb >> 3, r = nb & 7;
-  const int x = b & 7, i = b >> 3;
-  return x * q + (x < r ? x : r) + i;
-}
-
-// The same with chunks of kXcdChunk consecutive tiles dealt to the XCDs in
-// turn: every XCD gets a share of each part of the image, so one whose part is
-// dense does not end last. The barrier-free backward is 2 to 5 % faster with
-// chunks of 4 to 16 tiles than with one run per XCD (1200x680 / 500K: 179 ->
-// 176 us, 640x480: 121 -> 118; with 48 tiles 640x480 takes 128); the
-// forward, whose workgroups share their fetches, is not.
+// Work index of a workgroup. Workgroups are dealt round-robin to the 8 XCDs
+// (each with its own L2); this deals chunks of kXcdChunk consecutive indices to
+// them in turn: neighbours share an XCD's L2, and every XCD gets a share of
+// each part of the work, so one whose part is dense does not end last.
 constexpr int kXcdChunk = 16;
 __device__ __forceinline__ int xcd_chunk(int b, int nb) {
   const int full = nb / (8 * kXcdChunk) * (8 * kXcdChunk);
@@ -229,6 +218,7 @@ struct BinArgs {
   uint32_t* M;             // [n_items][n_wg]
   uint32_t* T;             // [n_items] pair totals; zero between launches
   int2* R;                 // [n_items] unclipped ranges
+  int* order;              // [n_items] items from the longest list to the shortest
   uint32_t* ticket;        // zero between launches
   uint32_t* K;             // overlap count
   uint32_t* K_host;        // NULL or a device-visible host word that also receives K
@@ -258,7 +248,7 @@ struct FwdArgs {
   unsigned long long* stats;  // non-NULL: count work only, write no outputs
   int n_items;                // views * tiles; item = view * n_tiles + tile
   int* queue;                 // persistent launch: work counter (zeroed first)
-  const int* order;           // persistent launch: item order (NULL = identity)
+  const int* order;           // [n_items] the items in the order they are taken
   int blocks;                 // persistent launch: workgroups (0 = one per item)
 };
 void launch_render_fwd(const Raster& R, const FwdArgs& a, hipStream_t s);
@@ -367,9 +357,6 @@ struct PoseAdam {
 // pose7 (in place) with the gradient just formed.
 void launch_pose_finalize(const float* pose7, const float* pose_acc, int64_t blocks, float* dL_dpose7,
                           float* dL_dtwist6, int n_views, hipStream_t s, const PoseAdam* adam = nullptr);
-// Longest-list-first order of (view, tile) items for the persistent launches
-// (power-of-two length buckets). temp: 64 ints.
-void launch_item_order(const int2* ranges, int n_items, int* order, int* temp, hipStream_t s);
 
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 void launch_fill_f32(float* p, float v, int64_t n, hipStream_t s);

@@ -34,9 +34,9 @@
 // A deterministic variant stores the wave's sums per (list position, block)
 // instead and a second pass adds them per Gaussian in a fixed order.
 //
-// Launch shapes: one workgroup per item (items dealt to XCDs in contiguous
-// runs), or a persistent grid whose workgroups pull items from a counter in
-// longest-list-first order until the queue is empty (multi-keyframe mapping).
+// Launch shapes, both from the longest list to the shortest: one workgroup per
+// item, or a persistent grid whose workgroups pull items from a counter until
+// the queue is empty (multi-keyframe mapping).
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -650,13 +650,13 @@ template <bool STATS>
 __global__ __launch_bounds__(kTileThreads) void k_render_fwd(Raster Rr, FwdArgs a) {
   __shared__ FwdSmem sm;
   init_smem(sm);
-  fwd_item<STATS>(Rr, a, xcd_tile(blockIdx.x, gridDim.x), sm);
+  fwd_item<STATS>(Rr, a, a.order[blockIdx.x], sm);
 }
 
 template <int NF, BwdSums SUMS>
 __global__ __launch_bounds__(kTileThreads, 5) void k_render_bwd(Raster Rr, BwdArgs a) {
   __shared__ BwdWave sm[kWavesPerTile];
-  bwd_item<NF, SUMS>(Rr, a, xcd_chunk((int)blockIdx.x, (int)gridDim.x), sm);
+  bwd_item<NF, SUMS>(Rr, a, a.order[blockIdx.x], sm);
 }
 
 // Persistent workgroups: take the next item from the queue until it is empty.
@@ -667,7 +667,7 @@ __device__ __forceinline__ int next_item(int* queue, const int* order, int n_ite
   __syncthreads();
   const int qi = *s_item;
   if (qi >= n_items) return -1;
-  return order ? order[qi] : qi;
+  return order[qi];
 }
 
 __global__ __launch_bounds__(kTileThreads) void k_render_fwd_persistent(Raster Rr, FwdArgs a) {
@@ -760,63 +760,6 @@ __global__ __launch_bounds__(kTileThreads) void k_count_bwd_pairs(Raster Rr, Fwd
   if ((threadIdx.x & 63) == 0) atomicAdd(&a.stats[2], n);
 }
 
-// Longest-list-first item order: bucket items by floor(log2(len + 1)) and
-// emit the buckets from the longest down (order inside a bucket is arbitrary).
-// Each wave aggregates its items per bucket (one leader lane per distinct
-// bucket), so the 32 global counters see one atomic per (wave, bucket)
-// instead of one per item.
-__device__ __forceinline__ int order_bucket(const int2* __restrict__ ranges, int i) {
-  const int2 r = ranges[i];
-  return 31 - __clz(r.y - r.x + 1);
-}
-
-__global__ void k_order_hist(const int2* __restrict__ ranges, int n_items, int* __restrict__ temp) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x & 63;
-  const bool valid = i < n_items;
-  const int b = valid ? order_bucket(ranges, i) : -1;
-  uint64_t remaining = __ballot(valid);
-  while (remaining) {
-    const int leader = __builtin_ctzll(remaining);
-    const int lb = __shfl(b, leader, 64);
-    const uint64_t same = __ballot(valid && b == lb);
-    if (lane == leader) atomicAdd(&temp[lb], __popcll(same));
-    remaining &= ~same;
-  }
-}
-
-__global__ void k_order_scan(int* temp) {
-  if (threadIdx.x != 0) return;
-  int s = 0;
-  for (int b = 31; b >= 0; --b) {
-    const int c = temp[b];
-    temp[32 + b] = s;
-    s += c;
-  }
-}
-
-__global__ void k_order_scatter(const int2* __restrict__ ranges, int n_items, int* __restrict__ temp,
-                                int* __restrict__ order) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x & 63;
-  const bool valid = i < n_items;
-  const int b = valid ? order_bucket(ranges, i) : -1;
-  uint64_t remaining = __ballot(valid);
-  while (remaining) {
-    const int leader = __builtin_ctzll(remaining);
-    const int lb = __shfl(b, leader, 64);
-    const uint64_t same = __ballot(valid && b == lb);
-    int base = 0;
-    if (lane == leader) base = atomicAdd(&temp[32 + lb], __popcll(same));
-    base = __shfl(base, leader, 64);
-    if (valid && b == lb) {
-      const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-      order[base + rank] = i;
-    }
-    remaining &= ~same;
-  }
-}
-
 }  // namespace
 
 void launch_render_fwd(const Raster& R, const FwdArgs& a, hipStream_t s) {
@@ -868,14 +811,6 @@ void launch_det_reduce(const int4* rect, const uint32_t* goff, const uint32_t* r
     hipLaunchKernelGGL(k_det_reduce<6>, dim3(g), dim3(256), 0, s, rect, goff, rev, mask, part, n_rec, g2d);
   else
     hipLaunchKernelGGL(k_det_reduce<10>, dim3(g), dim3(256), 0, s, rect, goff, rev, mask, part, n_rec, g2d);
-}
-
-void launch_item_order(const int2* ranges, int n_items, int* order, int* temp, hipStream_t s) {
-  launch_fill_u32(reinterpret_cast<uint32_t*>(temp), 0u, 64, s);
-  const unsigned g = (unsigned)((n_items + 255) / 256);
-  hipLaunchKernelGGL(k_order_hist, dim3(g), dim3(256), 0, s, ranges, n_items, temp);
-  hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(64), 0, s, temp);
-  hipLaunchKernelGGL(k_order_scatter, dim3(g), dim3(256), 0, s, ranges, n_items, temp, order);
 }
 
 }  // namespace gsr

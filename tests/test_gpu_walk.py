@@ -80,3 +80,36 @@ def test_non_finite_upstream_stays_in_its_pixel():
     for k in ("means", "scales", "quats", "opacities"):
         np.testing.assert_array_equal(got[k][clean], want[k][clean], err_msg=k)
     np.testing.assert_array_equal(got["colors"][px == 13], want["colors"][px == 13])
+
+
+@pytest.mark.parametrize("ntx,nty", [(16, 16), (257, 1), (64, 128), (211, 39)])
+def test_every_tile_is_rendered_in_any_order(ntx, nty):
+    """Tile counts around the 256 up to which the tiles keep their order and the
+    8,192 the ordering takes at a time, lists of 0 to a few hundred: one pixel
+    of every tile against the oracle (the bar of test_gpu_fullsize)."""
+    import torch
+    W, Hh, n_tiles = 16 * ntx, 16 * nty, ntx * nty
+    cam = oracle.Camera(W, Hh, 400.0, 400.0, W / 2, Hh / 2, 0.2, (0.0, 0.0, 0.0))
+    rng = np.random.default_rng(n_tiles)
+    tile = np.concatenate([np.flatnonzero(rng.uniform(size=n_tiles) < 0.9), np.full(300, n_tiles // 3),
+                           rng.integers(0, n_tiles, 2000)])
+    n = len(tile)
+    u, v = 16 * (tile % ntx) + 8, 16 * (tile // ntx) + 8
+    z = 2.0 + 1e-3 * rng.permutation(n)
+    g = G.f32(dict(means=np.stack([(u - W / 2) / 400 * z, (v - Hh / 2) / 400 * z, z], 1),
+                   scales=np.repeat((rng.uniform(0.5, 1.5, n) * z / 400)[:, None], 3, 1),
+                   quats=np.tile([1.0, 0, 0, 0], (n, 1)), opacities=rng.uniform(0.02, 0.4, n),
+                   colors=rng.uniform(0, 1, (n, 3))))
+    d = G.to_dev(g)
+    color, depth, alpha, st = gsr.render_fwd(d["means"], d["scales"], d["quats"], d["opacities"], d["colors"],
+                                             torch.tensor(POSE.astype(np.float32), device="cuda"),
+                                             gsr.make_camera(W, Hh, 400.0, 400.0, W / 2, Hh / 2, 0.2))
+    torch.cuda.synchronize()
+    st.release()
+    t = np.arange(n_tiles)
+    yy, xx = 16 * (t // ntx) + 8, 16 * (t % ntx) + 8
+    orc = oracle.render(g, POSE, cam, oracle.Opts(amb_rel=2e-4, amb_z=5e-7), pixels=yy * W + xx, nthreads=8)
+    pick = lambda a: a[..., yy, xx]
+    G.compare_images({k: pick(a.cpu().numpy()) for k, a in (("color", color), ("depth", depth), ("alpha", alpha))},
+                     {k: pick(a) for k, a in orc.items() if k != "hash"}, dict(color=1e-4, depth=1e-4, alpha=1e-4),
+                     max_unverifiable=0.02)
