@@ -482,6 +482,12 @@ void enqueue_front(gsr_ctx* c, gsr_state* s, hipStream_t st, uint32_t* K_host = 
   }
 }
 
+// The persistent grid of a compositing pass of which a compute unit holds
+// `held` workgroups; 0: one workgroup per item.
+int persistent_blocks(const gsr_ctx* c, const gsr_state* s, int held) {
+  return s->blocks < held * c->n_cu ? s->blocks : 0;
+}
+
 // Tile lists (ranges, slot placement, per-tile depth sort) and compositing.
 // cap bounds the overlap positions: the exact K (eager) or the capacity
 // (captured graphs, where an overflow is flagged on the device).
@@ -494,7 +500,7 @@ void enqueue_back(gsr_ctx* c, gsr_state* s, hipStream_t st, int64_t cap, float* 
   }
   gsr::FwdArgs fa{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz,
                   color, depth, alpha, s->Tfin, s->last, nullptr,
-                  n_items, s->queue, s->order, s->blocks};
+                  n_items, s->queue, s->order, persistent_blocks(c, s, gsr::kFwdHeld)};
   {
     Stage t(c, "render_fwd");
     gsr::launch_render_fwd(R, fa, st);
@@ -513,7 +519,8 @@ void enqueue_bwd(gsr_ctx* c, gsr_state* s, hipStream_t st, const float* gC, cons
   const bool geom_only = !adam && (!grads || (!grads->opacities && !grads->colors));
   const bool wide = !s->det && s->n * s->n_views <= gsr::kWideSums;
   gsr::BwdArgs ba{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz, s->Tfin, s->last,
-                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, s->order, s->blocks,
+                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, s->order,
+                  persistent_blocks(c, s, gsr::kBwdHeld),
                   nullptr, nullptr};
   if (s->det) {
     // arena D is in place (ensure_D): list positions of every (record, tile),

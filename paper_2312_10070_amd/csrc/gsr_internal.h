@@ -253,6 +253,14 @@ struct FwdArgs {
 };
 void launch_render_fwd(const Raster& R, const FwdArgs& a, hipStream_t s);
 
+// Workgroups of the compositing passes that a compute unit holds (forward: 26
+// of its 160 KB of LDS each; backward: 20 waves of at most 96 registers). A
+// persistent grid of as many or more per compute unit bounds nothing, and one
+// workgroup per item is faster, as no workgroup waits for its slowest wave
+// between items: 8 views of 1200x680, 1M Gaussians, 474 -> 358 us forward
+// and 986 -> 880 us backward. A smaller grid is run as asked for.
+constexpr int kFwdHeld = 6, kBwdHeld = 5;
+
 // The compositing backward adds a Gaussian's sums with atomics, in an order
 // that varies from run to run. Up to this many (Gaussian, view) pairs the
 // sums are doubles, which makes the results all but independent of the order;

@@ -164,6 +164,16 @@ __device__ __forceinline__ Chunk bin_chunk(const Raster& Rr, const BinArgs& a) {
 constexpr int kOrderBuckets = 512;
 // Compute units of the chip: up to as many items need no order.
 constexpr int kUnits = 256;
+// Workgroups a compute unit holds of the backward. Up to as many rounds of
+// items are all dealt out at the start, in turn over the compute units, and
+// none moves later. Each full round then goes out shortest first, so that the
+// units that get no item of the last, partial round are those with the longest
+// of each round before: backward 640x480 (4.7 rounds) of 500K 120 -> 114 us, of
+// 300K 90 -> 84 us (the sums of the lists' lengths per unit come to 1.14 of
+// their mean instead of 1.24), forward 66 -> 68 and 41 -> 40. With 6.8 rounds
+// (801x533) nothing changes.
+constexpr int kHeldRounds = 5;
+static_assert((kUnits & (kUnits - 1)) == 0, "a round is reversed by flipping its index bits");
 __device__ __forceinline__ int order_bucket(uint32_t len) {
   const int b = (int)(__float_as_uint((float)len) >> 19) - (127 << 4);
   return kOrderBuckets - 1 - max(b, 0);
@@ -172,8 +182,8 @@ __device__ __forceinline__ int order_bucket(uint32_t len) {
 // One workgroup: R[i] = (start, start + T[i]) with start the exclusive scan of
 // the tile totals T[0, n) (read at the device-coherent level), T[i] = 0, and
 // order = the items from the longest list to the shortest, by buckets (the
-// order inside a bucket is arbitrary); returns the sum. bins: kOrderBuckets
-// words of LDS.
+// order inside a bucket is arbitrary), few items with each round of kUnits
+// reversed; returns the sum. bins: kOrderBuckets words of LDS.
 // The sort and both compositing passes take the items in that order: a long
 // list that starts last is what a launch of a few items per compute unit ends
 // with, and runs of neighbouring tiles on one XCD, whose shared records its L2
@@ -232,7 +242,11 @@ __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t*
     }
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i)
-      if (base + i < n) order[atomicAdd(&bins[order_bucket(v[i])], 1u)] = (int)(base + i);
+      if (base + i < n) {
+        uint32_t p = atomicAdd(&bins[order_bucket(v[i])], 1u);
+        if (n <= kHeldRounds * kUnits && (int64_t)((p | (kUnits - 1)) + 1) <= n) p ^= kUnits - 1;
+        order[p] = (int)(base + i);
+      }
   }
   return carry;
 }
