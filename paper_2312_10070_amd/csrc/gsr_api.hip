@@ -45,6 +45,7 @@ struct gsr_state {
   float* pose_acc = nullptr;  // [views][projection-backward workgroups][12]
   int* queue = nullptr;       // persistent-launch work counter
   int* order = nullptr;       // [views * tiles] longest-list-first item order
+  bool by_length = false;     // the forward's passes go by it
   int n_views = 1;
   int blocks = 0;             // persistent workgroups (0 = one per item)
   // arena B: per overlap
@@ -494,13 +495,14 @@ int persistent_blocks(const gsr_ctx* c, const gsr_state* s, int held) {
 void enqueue_back(gsr_ctx* c, gsr_state* s, hipStream_t st, int64_t cap, float* color, float* depth, float* alpha) {
   const gsr::Raster& R = s->R;
   const int n_items = R.n_tiles * s->n_views;
+  s->by_length = gsr::order_pays(n_items, cap);
   {
     Stage t(c, "tile_bins");
     gsr::launch_tile_bins(R, bin_args(s, cap), n_items, s->ranges, s->scratch, s->ids, st);
   }
   gsr::FwdArgs fa{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz,
                   color, depth, alpha, s->Tfin, s->last, nullptr,
-                  n_items, s->queue, s->order, persistent_blocks(c, s, gsr::kFwdHeld)};
+                  n_items, s->queue, s->by_length ? s->order : nullptr, persistent_blocks(c, s, gsr::kFwdHeld)};
   {
     Stage t(c, "render_fwd");
     gsr::launch_render_fwd(R, fa, st);
@@ -519,7 +521,7 @@ void enqueue_bwd(gsr_ctx* c, gsr_state* s, hipStream_t st, const float* gC, cons
   const bool geom_only = !adam && (!grads || (!grads->opacities && !grads->colors));
   const bool wide = !s->det && s->n * s->n_views <= gsr::kWideSums;
   gsr::BwdArgs ba{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz, s->Tfin, s->last,
-                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, s->order,
+                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, s->by_length ? s->order : nullptr,
                   persistent_blocks(c, s, gsr::kBwdHeld),
                   nullptr, nullptr};
   if (s->det) {
@@ -1499,7 +1501,7 @@ int gsr_state_stats(gsr_ctx* c, gsr_state* s, int64_t out[6]) {
   GSR_HIP(c, hipMemsetAsync(c->d_stats, 0, 64, st));
   gsr::FwdArgs fa{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz,
                   nullptr, nullptr, nullptr, nullptr, s->last, c->d_stats,
-                  s->R.n_tiles * s->n_views, nullptr, s->order, 0};
+                  s->R.n_tiles * s->n_views, nullptr, nullptr, 0};
   gsr::launch_render_fwd(s->R, fa, st);
   unsigned long long h[3] = {0, 0, 0};
   GSR_HIP(c, hipMemcpyAsync(h, c->d_stats, sizeof(h), hipMemcpyDeviceToHost, st));

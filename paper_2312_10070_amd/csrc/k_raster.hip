@@ -34,8 +34,8 @@
 // A deterministic variant stores the wave's sums per (list position, block)
 // instead and a second pass adds them per Gaussian in a fixed order.
 //
-// Launch shapes, both from the longest list to the shortest: one workgroup per
-// item, or a persistent grid whose workgroups pull items from a counter until
+// Launch shapes, both from the longest list to the shortest where that pays
+// (see order_pays): one workgroup per item, or a persistent grid whose workgroups pull items from a counter until
 // the queue is empty (multi-keyframe mapping).
 #include "gsr_internal.h"
 
@@ -650,13 +650,15 @@ template <bool STATS>
 __global__ __launch_bounds__(kTileThreads) void k_render_fwd(Raster Rr, FwdArgs a) {
   __shared__ FwdSmem sm;
   init_smem(sm);
-  fwd_item<STATS>(Rr, a, a.order[blockIdx.x], sm);
+  const int b = (int)blockIdx.x;
+  fwd_item<STATS>(Rr, a, a.order ? a.order[b] : xcd_tile(b, (int)gridDim.x), sm);
 }
 
 template <int NF, BwdSums SUMS>
 __global__ __launch_bounds__(kTileThreads, 5) void k_render_bwd(Raster Rr, BwdArgs a) {
   __shared__ BwdWave sm[kWavesPerTile];
-  bwd_item<NF, SUMS>(Rr, a, a.order[blockIdx.x], sm);
+  const int b = (int)blockIdx.x;
+  bwd_item<NF, SUMS>(Rr, a, a.order ? a.order[b] : xcd_chunk(b, (int)gridDim.x), sm);
 }
 
 // Persistent workgroups: take the next item from the queue until it is empty.
@@ -667,7 +669,7 @@ __device__ __forceinline__ int next_item(int* queue, const int* order, int n_ite
   __syncthreads();
   const int qi = *s_item;
   if (qi >= n_items) return -1;
-  return order[qi];
+  return order ? order[qi] : qi;
 }
 
 __global__ __launch_bounds__(kTileThreads) void k_render_fwd_persistent(Raster Rr, FwdArgs a) {

@@ -162,8 +162,7 @@ __device__ __forceinline__ Chunk bin_chunk(const Raster& Rr, const BinArgs& a) {
 
 // Bucket of a list length, longest first: 16 buckets per power of two.
 constexpr int kOrderBuckets = 512;
-// Compute units of the chip: up to as many items need no order.
-constexpr int kUnits = 256;
+constexpr int kUnits = 256;  // compute units of the chip
 // Workgroups a compute unit holds of the backward. Up to as many rounds of
 // items are all dealt out at the start, in turn over the compute units, and
 // none moves later. Each full round then goes out shortest first, so that the
@@ -179,6 +178,18 @@ __device__ __forceinline__ int order_bucket(uint32_t len) {
   return kOrderBuckets - 1 - max(b, 0);
 }
 
+// The totals of items base .. base + kScanItems - 1 back from the ranges this
+// thread wrote, unless they are still in v.
+__device__ __forceinline__ void last_totals(const int2* R, int64_t base, int64_t n, bool reload,
+                                            uint32_t (&v)[kScanItems]) {
+  if (!reload) return;
+  int2 r[kScanItems];
+#pragma unroll
+  for (int i = 0; i < kScanItems; ++i) r[i] = R[base + i < n ? base + i : n - 1];
+#pragma unroll
+  for (int i = 0; i < kScanItems; ++i) v[i] = (uint32_t)(r[i].y - r[i].x);
+}
+
 // One workgroup: R[i] = (start, start + T[i]) with start the exclusive scan of
 // the tile totals T[0, n) (read at the device-coherent level), T[i] = 0, and
 // order = the items from the longest list to the shortest, by buckets (the
@@ -192,11 +203,10 @@ __device__ __forceinline__ int order_bucket(uint32_t len) {
 // 1M 138 -> 115 us forward; of 500K 98 -> 89 and 201 -> 185; 801x533 of 200K
 // 46 -> 43 and 93 -> 85; 640x480 of 500K 77.6 -> 66.6 and 119 (the same). The
 // order costs this kernel 1.7 us (25,800 items: 18, as three kernels of its own
-// 55); where every item has a compute unit to itself it is left out.
+// 55), and reading it each of the three passes some more: see order_pays.
 __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t* bins, int64_t n) {
   __shared__ uint32_t s_wave[kPlaceThreads / 64];
   static_assert(kOrderBuckets <= kPlaceThreads, "one bucket per thread");
-  const bool sorted = n > kUnits;
   if (threadIdx.x < kOrderBuckets) bins[threadIdx.x] = 0;
   uint32_t carry = 0;
   uint32_t v[kScanItems];
@@ -214,32 +224,34 @@ __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t*
     for (int i = 0; i < kScanItems; ++i) {
       if (base + i < n) {
         R[base + i] = make_int2((int)ex, (int)(ex + v[i]));
-        if (sorted) atomicAdd(&bins[order_bucket(v[i])], 1u);
-        else order[base + i] = (int)(base + i);
         __hip_atomic_store(T + base + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       ex += v[i];
     }
     carry += tot;
   }
-  if (!sorted) return carry;
+  if (!order_pays(n, carry)) {  // few or short lists: the order they are in, where a launch may ask for one
+    if (n > kOrderItems)
+      for (int64_t i = threadIdx.x; i < n; i += kPlaceThreads) order[i] = (int)i;
+    return carry;
+  }
+  constexpr int64_t kStretch = (int64_t)kPlaceThreads * kScanItems;
+  for (int64_t b0 = (n - 1) / kStretch * kStretch; b0 >= 0; b0 -= kStretch) {
+    const int64_t base = b0 + (int64_t)threadIdx.x * kScanItems;
+    last_totals(R, base, n, b0 + kStretch < n, v);
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i)
+      if (base + i < n) atomicAdd(&bins[order_bucket(v[i])], 1u);
+  }
   __syncthreads();
   uint32_t tot;
   const uint32_t first =
       block_exclusive_scan_t<kPlaceThreads>(threadIdx.x < kOrderBuckets ? bins[threadIdx.x] : 0u, &tot, s_wave);
   if (threadIdx.x < kOrderBuckets) bins[threadIdx.x] = first;
   __syncthreads();
-  // the last stretch's totals are still in v; an earlier one's come from R
-  constexpr int64_t kStretch = (int64_t)kPlaceThreads * kScanItems;
-  for (int64_t b0 = (n - 1) / kStretch * kStretch; b0 >= 0; b0 -= kStretch) {
+  for (int64_t b0 = 0; b0 < n; b0 += kStretch) {
     const int64_t base = b0 + (int64_t)threadIdx.x * kScanItems;
-    if (b0 + kStretch < n) {
-      int2 r[kScanItems];
-#pragma unroll
-      for (int i = 0; i < kScanItems; ++i) r[i] = R[base + i];  // (this thread's own writes)
-#pragma unroll
-      for (int i = 0; i < kScanItems; ++i) v[i] = (uint32_t)(r[i].y - r[i].x);
-    }
+    last_totals(R, base, n, n > kStretch, v);
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i)
       if (base + i < n) {
@@ -467,10 +479,13 @@ __global__ __launch_bounds__(kBinThreads) void k_tile_sort(const int2* __restric
   constexpr int kItems = kBinThreads / 64;
   constexpr int kLongRun = 1024;
   const int w = threadIdx.x >> 6;
-  // the workgroup's it-th item: one of each quarter of the order, so that no
-  // workgroup gets several of the longest (order: 25,800 lists, 138 -> 103 us)
-  auto at = [&](int it) { return (int64_t)blockIdx.x + (int64_t)it * gridDim.x; };
-  auto range = [&](int it) { return ranges[order[at(it)]]; };
+  // the workgroup's it-th item: four neighbours, or with an order one of each
+  // quarter of it, so that no workgroup gets several of the longest (25,800
+  // lists, 138 -> 103 us)
+  auto at = [&](int it) {
+    return order ? (int64_t)blockIdx.x + (int64_t)it * gridDim.x : (int64_t)blockIdx.x * kItems + it;
+  };
+  auto range = [&](int it) { return ranges[order ? order[at(it)] : at(it)]; };
   if (at(w) < n_items) {
     const int2 rg = range(w);
     const int len = rg.y - rg.x;
@@ -589,7 +604,8 @@ void launch_tile_bins(const Raster& R, const BinArgs& a, int64_t n_items, int2* 
   b.ranges = ranges;
   hipLaunchKernelGGL(k_bin_place, bin_grid(R, b), dim3(kPlaceThreads), bin_lds(R), s, R, b);
   hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)((n_items + kBinThreads / 64 - 1) / (kBinThreads / 64))),
-                     dim3(kBinThreads), 0, s, (const int2*)ranges, n_items, a.keys, scratch, ids, (const int*)a.order);
+                     dim3(kBinThreads), 0, s, (const int2*)ranges, n_items, a.keys, scratch, ids,
+                     order_pays(n_items, a.cap) ? (const int*)a.order : (const int*)nullptr);
 }
 
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s) {

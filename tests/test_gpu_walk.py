@@ -113,3 +113,33 @@ def test_every_tile_is_rendered_in_any_order(ntx, nty):
     G.compare_images({k: pick(a.cpu().numpy()) for k, a in (("color", color), ("depth", depth), ("alpha", alpha))},
                      {k: pick(a) for k, a in orc.items() if k != "hash"}, dict(color=1e-4, depth=1e-4, alpha=1e-4),
                      max_unverifiable=0.02)
+
+
+@pytest.mark.parametrize("V", [3, 6, 33])
+def test_lists_by_length_give_what_lists_in_place_give(V):
+    """Views of 256 tiles: one by one their lists are taken as they lie; as one
+    batch (768 items: rounds reversed; 1,536; 8,448: ordered in two stretches)
+    by length. A tile's pixels do not depend on the order, so the images are
+    equal to the bit."""
+    import torch
+    rng = np.random.default_rng(V)
+    n = 20000
+    z = rng.uniform(2.0, 4.0, n)
+    g = G.to_dev(dict(means=np.stack([rng.uniform(-0.35, 0.35, n) * z, rng.uniform(-0.35, 0.35, n) * z, z], 1),
+                      scales=np.repeat((rng.uniform(2.0, 12.0, n) * z / 400)[:, None], 3, 1),
+                      quats=np.tile([1.0, 0, 0, 0], (n, 1)), opacities=rng.uniform(0.02, 0.9, n),
+                      colors=rng.uniform(0, 1, (n, 3))))
+    args = [g[k] for k in ("means", "scales", "quats", "opacities", "colors")]
+    camera = gsr.make_camera(256, 256, 400.0, 400.0, 128.0, 128.0, 0.2)
+    poses = np.tile(POSE, (V, 1))
+    poses[:, 4] = np.linspace(-0.2, 0.2, V)
+    poses = torch.from_numpy(poses.astype(np.float32)).cuda()
+    cb, db, ab, st = gsr.render_fwd_batch(*args, poses, camera, gsr.RasterOpts())
+    K = gsr.tile_lists(st, 256 * V)[0]
+    st.release()
+    assert 1 << 18 <= K < V << 18  # by length as one batch, as they lie one by one
+    for v in range(V):
+        c, d, a, st = gsr.render_fwd(*args, poses[v].contiguous(), camera)
+        assert gsr.tile_lists(st, 256)[0] < 1 << 18
+        st.release()
+        assert torch.equal(cb[v], c) and torch.equal(db[v], d) and torch.equal(ab[v], a)
