@@ -32,7 +32,7 @@ struct gsr_state {
   int4* rect = nullptr;
   uint32_t* counts = nullptr;
   int n_wg = 1;                    // binning workgroups per view
-  uint32_t* bin_M = nullptr;       // [items][n_wg]: a workgroup's offset inside a (view, tile) range
+  uint32_t* bin_M = nullptr;       // [views][n_wg][tiles]: a workgroup's offset inside a (view, tile) range
   uint32_t* bin_T = nullptr;       // [items]: pair totals (zero between forwards)
   int2* bin_R = nullptr;           // [items]: unclipped ranges
   uint32_t* bin_ticket = nullptr;  // zero between forwards
@@ -212,7 +212,7 @@ void carve_B(gsr_state* s, char* base, int64_t K, size_t* bytes) {
 }
 
 int ensure_A(gsr_ctx* c, gsr_state* s, int64_t n, int64_t P, int64_t tiles, int64_t views) {
-  const int64_t nm_req = tiles * gsr::bin_workgroups(n / std::max<int64_t>(views, 1));
+  const int64_t nm_req = tiles * gsr::bin_workgroups(n / std::max<int64_t>(views, 1), views);
   if (s->arenaA && n <= s->n_cap && P <= s->P_cap && tiles <= s->tiles_cap && views <= s->views_cap &&
       nm_req <= s->bin_cap)
     return GSR_OK;
@@ -220,7 +220,7 @@ int ensure_A(gsr_ctx* c, gsr_state* s, int64_t n, int64_t P, int64_t tiles, int6
   s->arenaA = nullptr;
   const int64_t nn = std::max<int64_t>(n + n / 4, 1024), PP = std::max<int64_t>(P, 256),
                 tt = std::max<int64_t>(tiles, 16), vv = std::max<int64_t>(views, 1);
-  const int64_t nm = std::max<int64_t>(tt * gsr::bin_workgroups(nn / vv), nm_req);
+  const int64_t nm = std::max<int64_t>(tt * gsr::bin_workgroups(nn / vv, vv), nm_req);
   size_t bytes = 0;
   carve_A(s, nullptr, nn, PP, tt, vv, nm, &bytes);
   void* p = nullptr;
@@ -478,7 +478,7 @@ void enqueue_front(gsr_ctx* c, gsr_state* s, hipStream_t st, uint32_t* K_host = 
   }
   {
     Stage t(c, "bin_count");
-    s->n_wg = gsr::bin_workgroups(s->n);
+    s->n_wg = gsr::bin_workgroups(s->n, s->n_views);
     gsr::launch_bin_count(s->R, bin_args(s, 0, K_host), st);
   }
 }

@@ -216,8 +216,10 @@ void launch_prune(const PruneArgs& a, int64_t n, float thre, const int32_t* mask
                   hipStream_t s);
 
 // Tile binning (see k_sort.hip). Workgroup w of view v handles the Gaussians
-// [w c, (w + 1) c) with c = ceil(n / n_wg); M[item][w] is the offset of its
-// pairs inside the range of the (view, tile) item, R[item] that range.
+// [w c, (w + 1) c) with c = ceil(n / n_wg); M[v][w][tile] is the offset of
+// its pairs inside the range of the (view, tile) item, R[item] that range (a
+// workgroup's offsets lie side by side: written and read in runs, 1200x680 of
+// 1M 24 -> 20 us counting and 24 -> 21 placing against [item][w]).
 // rect[o] = (tx0 | tx1 << 16, ty0 | ty1 << 16, float bits of the camera
 // depth, number of tiles; 0 = not binned): everything binning reads, 16 bytes.
 struct BinArgs {
@@ -225,7 +227,7 @@ struct BinArgs {
   int n_views;
   int n_wg;                // workgroups per view
   const int4* rect;
-  uint32_t* M;             // [n_items][n_wg]
+  uint32_t* M;             // [n_views][n_wg][n_tiles]
   uint32_t* T;             // [n_items] pair totals; zero between launches
   int2* R;                 // [n_items] unclipped ranges
   int* order;              // [n_items] items from the longest list to the shortest
@@ -246,7 +248,12 @@ struct BinArgs {
 // plain order; a launch asks with the capacity, which is no smaller.
 constexpr int64_t kOrderItems = 512;
 __host__ __device__ __forceinline__ bool order_pays(int64_t n, int64_t K) { return n > kOrderItems && K >= 1 << 18; }
-int bin_workgroups(int64_t n);
+// Workgroups per view: 1,024 Gaussians each, at most 128, and over all views at
+// most about one per compute unit. Every workgroup reserves room on every tile
+// it meets, with an atomic on a word that all of the view's workgroups share:
+// 8 views of 1M, 128 per view 120 us counting and 98 placing, 64 109 and 98, 32
+// 98 and 92; one view, 256 instead of 128 24 us instead of 20 and 21 each.
+int bin_workgroups(int64_t n, int64_t views);
 // M, R and K from the tile rectangles (LDS histograms, one reservation atomic
 // per (tile, workgroup), the last workgroup scans the tile totals).
 void launch_bin_count(const Raster& R, const BinArgs& a, hipStream_t s);

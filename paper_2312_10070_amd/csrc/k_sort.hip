@@ -230,7 +230,7 @@ __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t*
     }
     carry += tot;
   }
-  if (!order_pays(n, carry)) {  // few or short lists: the order they are in, where a launch may ask for one
+  if (!order_pays(n, carry)) {  // few or short lists: as they lie, where a launch may ask for an order
     if (n > kOrderItems)
       for (int64_t i = threadIdx.x; i < n; i += kPlaceThreads) order[i] = (int)i;
     return carry;
@@ -263,7 +263,7 @@ __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t*
   return carry;
 }
 
-// Pairs per (tile, workgroup) in LDS; M[(v n_tiles + t) n_wg + w] = offset of
+// Pairs per (tile, workgroup) in LDS; M[(v n_wg + w) n_tiles + t] = offset of
 // workgroup w's pairs inside the range of tile t of view v (reserved with an
 // atomic on T, so the order of the workgroups inside a tile is arbitrary).
 // The last workgroup writes the ranges R, the item order and K.
@@ -291,9 +291,19 @@ __global__ __launch_bounds__(kPlaceThreads) void k_bin_count(Raster Rr, BinArgs 
   }
   __syncthreads();
   const int64_t row = view * Rr.n_tiles + c.t0;
-  for (int i = threadIdx.x; i < c.nt; i += blockDim.x) {
-    const uint32_t h = hist[i];
-    if (h) a.M[(row + i) * a.n_wg + blockIdx.x] = atomicAdd(a.T + row + i, h);
+  uint32_t* m = a.M + (view * a.n_wg + blockIdx.x) * Rr.n_tiles + c.t0;
+  // four reservations per thread and round: their atomics are in flight together
+  for (int i0 = threadIdx.x; i0 < c.nt; i0 += 4 * kPlaceThreads) {
+    uint32_t h[4], at[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * kPlaceThreads;
+      h[u] = i < c.nt ? hist[i] : 0u;
+      if (h[u]) at[u] = atomicAdd(a.T + row + i, h[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (h[u]) m[i0 + u * kPlaceThreads] = at[u];
   }
   __syncthreads();  // every reservation of the workgroup has returned
   if (threadIdx.x == 0) {
@@ -321,7 +331,9 @@ __global__ __launch_bounds__(kPlaceThreads) void k_bin_place(Raster Rr, BinArgs 
   const int64_t view = blockIdx.y;
   const int64_t row = view * Rr.n_tiles + c.t0;
   // (entries of tiles the workgroup has no pair on are not used)
-  for (int i = threadIdx.x; i < c.nt; i += blockDim.x) next[i] = (uint32_t)a.R[row + i].x + a.M[(row + i) * a.n_wg + blockIdx.x];
+  const uint32_t* m = a.M + (view * a.n_wg + blockIdx.x) * Rr.n_tiles + c.t0;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < c.nt; i += kPlaceThreads) next[i] = (uint32_t)a.R[row + i].x + m[i];
   // the chunk's tile ranges clipped to the capacity, tiles dealt round-robin
   // over the chunk's workgroups
   for (int i = (int)blockIdx.x + a.n_wg * (int)threadIdx.x; i < c.nt; i += a.n_wg * (int)blockDim.x) {
@@ -576,9 +588,10 @@ void launch_exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_
   hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, out, n, (const uint32_t*)temp);
 }
 
-int bin_workgroups(int64_t n) {
+int bin_workgroups(int64_t n, int64_t views) {
   const int64_t w = (n + 1023) / 1024;
-  return (int)(w < 1 ? 1 : (w > 128 ? 128 : w));
+  const int64_t most = std::max<int64_t>(16, std::min<int64_t>(128, kUnits / std::max<int64_t>(views, 1)));
+  return (int)(w < 1 ? 1 : (w > most ? most : w));
 }
 
 namespace {
