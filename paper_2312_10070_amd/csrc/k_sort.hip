@@ -1,18 +1,17 @@
 // Tile binning in two passes. Each binning workgroup owns a contiguous run of
 // Gaussians and counts their (Gaussian, tile) pairs per tile in an LDS
 // histogram; for every tile it meets it reserves a sub-range of the tile's
-// range with one atomic on the tile's total and keeps the offset in column w
-// of a [tile][workgroup] matrix M. The last workgroup to finish scans the
+// range with one atomic on the tile's total and keeps the offset in row w of a
+// [workgroup][tile] matrix M. The last workgroup to finish scans the
 // tile totals into the tiles' [start, end) ranges and the overlap count K
 // (and zeroes the totals for the next launch). The placing workgroup then
 // walks its Gaussians again, takes positions from LDS counters seeded with
 // start + its offset, and writes the keys (float bits of the camera depth <<
-// 32 | record index) in arbitrary order. Finally each
-// tile's range is sorted by key and its record indices written: by one wave
-// in registers (a bitonic network of up to 2048 keys), or for longer ranges
-// by the waves of a workgroup side by side (runs of 1024 keys, merged
-// pairwise in global memory). Keys are unique within a
-// tile, so the result is the depth order of the "m ordered Gaussians" of
+// 32 | record index) in arbitrary order. Finally each tile's range is sorted
+// by key and its record indices written: by one wave in registers (a bitonic
+// network of up to 1024 or 2048 keys), or for longer ranges by the waves of a
+// workgroup side by side (runs of half as many, merged pairwise in global
+// memory). Keys are unique within a tile, so the result is the depth order of the "m ordered Gaussians" of
 // Eq. 3 and Eq. 6 with ties broken by index: exactly what a stable sort of
 // (tile, depth) gives. No launch grid depends on K: positions at or beyond
 // the capacity are dropped and flagged, so the same launches serve captured
@@ -386,9 +385,6 @@ __device__ void merge_runs(const uint64_t* a, int na, const uint64_t* b, int nb,
   }
 }
 
-// Keys a single wave sorts in registers (up to 32 per lane).
-constexpr int kWaveSort = 2048;
-
 // The value of lane (lane ^ m) for m in {1, 2, 4, 8, 16, 32}, without LDS:
 // DPP quad_perm for 1 and 2, row_half_mirror then quad_perm [3,2,1,0] for 4
 // ((i ^ 7) ^ 3 = i ^ 4), row_ror:8 for 8 (a rotation by 8 of a 16-lane row is
@@ -430,13 +426,13 @@ __device__ __forceinline__ uint64_t lane_xor64(uint64_t v, int m) {
 // exchange with lane l ^ (stride / E). Writes the low words (record indices)
 // to ids (kKeys false) or the sorted keys to out_keys[b, b + len) (kKeys true).
 template <int E, bool kKeys = false>
-__device__ void wave_sort(const uint64_t* __restrict__ keys, int64_t b, int len, uint32_t* __restrict__ ids,
-                          uint64_t* __restrict__ out_keys = nullptr) {
+__device__ __forceinline__ void wave_sort(const uint64_t* __restrict__ keys, int64_t b, int len,
+                                          uint32_t* __restrict__ ids, uint64_t* __restrict__ out_keys = nullptr) {
   const int lane = threadIdx.x & 63;
   uint64_t e[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    const int i = E * lane + r;
+    const int i = kWave * r + lane;  // any order will do to begin with: whole lines
     e[r] = i < len ? keys[b + i] : ~0ull;  // padding sorts last (keys hold finite depths)
   }
 #pragma unroll
@@ -451,7 +447,7 @@ __device__ void wave_sort(const uint64_t* __restrict__ keys, int64_t b, int len,
           const bool asc = ((E * lane + r) & k) == 0;
           // (the 512-key network exchanges through DPP / permlane; the larger
           // ones through ds_bpermute, whose code stays smaller)
-          const uint64_t p = E == 8 ? lane_xor64(e[r], m) : __shfl_xor(e[r], m, 64);
+          const uint64_t p = E <= 8 ? lane_xor64(e[r], m) : __shfl_xor(e[r], m, 64);
           // the lower position keeps the minimum of an ascending block, the upper the maximum
           const bool keep_min = asc != upper;
           e[r] = ((e[r] < p) == keep_min) ? e[r] : p;
@@ -481,15 +477,24 @@ __device__ void wave_sort(const uint64_t* __restrict__ keys, int64_t b, int len,
 }
 
 // Four (view, tile) items per workgroup. Each wave sorts one item of at most
-// kWaveSort keys in registers (the smallest of the 512 / 1024 / 2048-key
+// kWaveSort keys in registers (the smallest of the 256 / 512 / 1024 / 2048-key
 // networks that holds it). Longer items are cut into runs of kLongRun keys,
-// which the workgroup's waves sort side by side into scratch (the 1024-key
-// network), and pairwise merges (ping-pong between scratch and keys) join.
+// which the workgroup's waves sort side by side into scratch, and pairwise
+// merges (ping-pong between scratch and keys) join.
+// Bound by the longest item's chain of exchanges. The 2048-key network takes 49
+// us, and its 133 registers (71 without it) leave three waves a SIMD to every
+// list; it serves a few long lists badly: 1200x680 of 1M (14 of 3,225 lists of
+// 1025 to 1075 keys) 49 -> 38 us with those in runs of 512, 8 views of it 112
+// -> 65. Where most lists are that long, a workgroup's merges one after the
+// other are worse (nine lists of 2000 keys 45 -> 78 us): kLong, up to 2048 keys
+// and runs of 1024, is for mean lengths above 1024. The 256-key network: lists
+// of 140 keys 9.6 -> 5.5 us. The keys are read in whole lines (38.4 against 39.0).
+template <bool kLong>
 __global__ __launch_bounds__(kBinThreads) void k_tile_sort(const int2* __restrict__ ranges, int64_t n_items,
                                                           uint64_t* __restrict__ keys, uint64_t* __restrict__ scratch,
                                                           uint32_t* __restrict__ ids, const int* __restrict__ order) {
   constexpr int kItems = kBinThreads / 64;
-  constexpr int kLongRun = 1024;
+  constexpr int kWaveSort = kLong ? 2048 : 1024, kLongRun = kWaveSort / 2;
   const int w = threadIdx.x >> 6;
   // the workgroup's it-th item: four neighbours, or with an order one of each
   // quarter of it, so that no workgroup gets several of the longest (25,800
@@ -501,12 +506,14 @@ __global__ __launch_bounds__(kBinThreads) void k_tile_sort(const int2* __restric
   if (at(w) < n_items) {
     const int2 rg = range(w);
     const int len = rg.y - rg.x;
-    if (len > 0 && len <= 512) {
+    if (len > 0 && len <= 256) {
+      wave_sort<4>(keys, rg.x, len, ids);
+    } else if (len > 256 && len <= 512) {
       wave_sort<8>(keys, rg.x, len, ids);
     } else if (len > 512 && len <= 1024) {
       wave_sort<16>(keys, rg.x, len, ids);
-    } else if (len > 1024 && len <= kWaveSort) {
-      wave_sort<32>(keys, rg.x, len, ids);
+    } else if (kLong && len > 1024 && len <= kWaveSort) {
+      wave_sort<kLong ? 32 : 16>(keys, rg.x, len, ids);
     }
   }
   // runs of the long items, dealt to the waves in turn
@@ -616,7 +623,8 @@ void launch_tile_bins(const Raster& R, const BinArgs& a, int64_t n_items, int2* 
   BinArgs b = a;
   b.ranges = ranges;
   hipLaunchKernelGGL(k_bin_place, bin_grid(R, b), dim3(kPlaceThreads), bin_lds(R), s, R, b);
-  hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)((n_items + kBinThreads / 64 - 1) / (kBinThreads / 64))),
+  const auto sort = a.cap > 1024 * n_items ? k_tile_sort<true> : k_tile_sort<false>;
+  hipLaunchKernelGGL(sort, dim3((unsigned)((n_items + kBinThreads / 64 - 1) / (kBinThreads / 64))),
                      dim3(kBinThreads), 0, s, (const int2*)ranges, n_items, a.keys, scratch, ids,
                      order_pays(n_items, a.cap) ? (const int*)a.order : (const int*)nullptr);
 }

@@ -143,3 +143,20 @@ def test_lists_by_length_give_what_lists_in_place_give(V):
         assert gsr.tile_lists(st, 256)[0] < 1 << 18
         st.release()
         assert torch.equal(cb[v], c) and torch.equal(db[v], d) and torch.equal(ab[v], a)
+
+
+@pytest.mark.parametrize("lengths", [[255, 256, 257, 511, 512, 1536, 1537, 1025, 2],
+                                     [2048, 2049, 3073, 1024, 1025, 256, 257, 4097, 3]])
+def test_sort_networks_and_runs(lengths):
+    """Lists around the 256-key network and the runs of 512 (mean length below
+    1,024), and around the 2048-key network and the runs of 1,024 (above):
+    bit-exact against the oracle, with depth ties."""
+    from tests.test_gpu_parity import run_fwd, tile_stacks
+    g, cam = tile_stacks(lengths, seed=3)
+    g = G.certify(g, POSE, cam, 1e-4)
+    tl = oracle.tile_lists(g, POSE, cam, oracle.Opts())
+    assert (tl["ranges"][:, 1] - tl["ranges"][:, 0]).tolist() == lengths
+    _, st, _, _ = run_fwd(g, POSE, cam)
+    K, ranges, ids = gsr.tile_lists(st, 9)
+    assert K == sum(lengths)
+    G.compare_tile_lists(ranges.cpu().numpy(), ids.cpu().numpy(), tl, None)
