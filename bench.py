@@ -59,9 +59,9 @@ def stage_work(stage: str, st: dict, n: int, P: int) -> tuple[str, float]:
     if stage == "render_bwd":
         return "alu", FLOPS_EVAL * st["pairs_bwd"] + FLOPS_COMP_BWD * st["pairs_composited"]
     if stage == "bin_count":
-        # packed rectangles read (16 B per Gaussian); the [tile][workgroup] matrix (128 workgroups) is
-        # written, scanned (read twice, written once) and read
-        return "hbm", n * 16.0 + st["tiles"] * 128 * 4.0 * 4
+        # packed rectangles read (16 B per Gaussian); the [workgroup][tile] matrix (128 workgroups) is
+        # written, and read by the placement
+        return "hbm", n * 16.0 + st["tiles"] * 128 * 4.0 * 2
     if stage == "tile_bins":
         # placement reads the packed rectangle with the depth (16 B per Gaussian) and writes an 8-B key per
         # overlap; the per-tile sort reads the key and writes a 4-B id
@@ -122,8 +122,8 @@ def read_traffic(stage: str, workload: str):
 
 
 # kernels of each stage, as rocprofv3 names them (prefix after the namespace)
-STAGE_KERNELS = {"render_bwd": ["k_render_bwd_block<false>("], "render_fwd": ["k_render_fwd<false>("],
-                 "tile_bins": ["k_bin_place(", "k_tile_sort("],
+STAGE_KERNELS = {"render_bwd": ["k_render_bwd<10,"], "render_fwd": ["k_render_fwd<false>("],
+                 "tile_bins": ["k_bin_place(", "k_tile_sort<"],
                  "bin_count": ["k_bin_count("],
                  "project": ["k_project("], "project_bwd_adam": ["k_project_bwd("],
                  "loss_ssim": ["k_loss_ssim("]}
@@ -215,9 +215,9 @@ VALU_PASSES = [
 ]
 N_CU = 256  # MI355X compute units
 # kernels of the tracking iteration, as rocprofv3 names them
-TRACK_KERNELS = {"render_bwd": ["k_render_bwd_quad<false>("], "render_fwd": ["k_render_fwd<false>("],
+TRACK_KERNELS = {"render_bwd": ["k_render_bwd<6,"], "render_fwd": ["k_render_fwd<false>("],
                  "project": ["k_project("], "project_bwd": ["k_project_bwd("], "bin_count": ["k_bin_count("],
-                 "tile_bins": ["k_bin_place(", "k_tile_sort("],
+                 "tile_bins": ["k_bin_place(", "k_tile_sort<"],
                  "loss_track": ["k_select_hist(", "k_loss_track("]}
 PROFILE_COMMANDS = {
     "H": ("python3 bench.py --steps 5 --warmup 2 --no-cpu-baseline --no-tracking --no-batched --no-initnet "
