@@ -45,7 +45,6 @@ struct gsr_state {
   float* pose_acc = nullptr;  // [views][projection-backward workgroups][12]
   int* queue = nullptr;       // persistent-launch work counter
   int* order = nullptr;       // [views * tiles] longest-list-first item order
-  bool by_length = false;     // the forward's passes go by it
   int n_views = 1;
   int blocks = 0;             // persistent workgroups (0 = one per item)
   // arena B: per overlap
@@ -467,6 +466,17 @@ gsr::BinArgs bin_args(gsr_state* s, int64_t cap, uint32_t* K_host = nullptr) {
                       s->order, s->bin_ticket, s->d_K, K_host, cap, s->keys, s->d_overflow};
 }
 
+// The persistent grid of a compositing pass of which a compute unit holds
+// `held` workgroups; 0: one workgroup per item.
+int persistent_blocks(const gsr_ctx* c, const gsr_state* s, int held) {
+  return s->blocks < held * c->n_cu ? s->blocks : 0;
+}
+
+// The order in which the passes take the items.
+gsr::ItemOrder item_order(const gsr_state* s) {
+  return {s->R.n_tiles * s->n_views > gsr::kOrderItems ? s->order : nullptr, s->d_K, gsr::kOrderEntries};
+}
+
 // Projection, per-(tile, workgroup) pair counts, the tiles' ranges and the
 // overlap count K (in s->d_K, and in *K_host when given).
 void enqueue_front(gsr_ctx* c, gsr_state* s, hipStream_t st, uint32_t* K_host = nullptr) {
@@ -483,26 +493,22 @@ void enqueue_front(gsr_ctx* c, gsr_state* s, hipStream_t st, uint32_t* K_host = 
   }
 }
 
-// The persistent grid of a compositing pass of which a compute unit holds
-// `held` workgroups; 0: one workgroup per item.
-int persistent_blocks(const gsr_ctx* c, const gsr_state* s, int held) {
-  return s->blocks < held * c->n_cu ? s->blocks : 0;
-}
-
 // Tile lists (ranges, slot placement, per-tile depth sort) and compositing.
-// cap bounds the overlap positions: the exact K (eager) or the capacity
-// (captured graphs, where an overflow is flagged on the device).
+// cap bounds the overlap positions: the exact K (a state's first forward) or
+// the workspace's capacity (later ones, and captured graphs, where an overflow
+// is flagged on the device). Only the placement looks at it.
 void enqueue_back(gsr_ctx* c, gsr_state* s, hipStream_t st, int64_t cap, float* color, float* depth, float* alpha) {
   const gsr::Raster& R = s->R;
   const int n_items = R.n_tiles * s->n_views;
-  s->by_length = gsr::order_pays(n_items, cap);
+  const int blocks = persistent_blocks(c, s, gsr::kFwdHeld);
+  const gsr::ItemOrder order = item_order(s);
   {
     Stage t(c, "tile_bins");
-    gsr::launch_tile_bins(R, bin_args(s, cap), n_items, s->ranges, s->scratch, s->ids, st);
+    gsr::launch_tile_bins(R, bin_args(s, cap), n_items, s->ranges, s->scratch, s->ids, order, st);
   }
   gsr::FwdArgs fa{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz,
                   color, depth, alpha, s->Tfin, s->last, nullptr,
-                  n_items, s->queue, s->by_length ? s->order : nullptr, persistent_blocks(c, s, gsr::kFwdHeld)};
+                  n_items, s->queue, order, blocks};
   {
     Stage t(c, "render_fwd");
     gsr::launch_render_fwd(R, fa, st);
@@ -520,9 +526,9 @@ void enqueue_bwd(gsr_ctx* c, gsr_state* s, hipStream_t st, const float* gC, cons
   // clears the sums it reads
   const bool geom_only = !adam && (!grads || (!grads->opacities && !grads->colors));
   const bool wide = !s->det && s->n * s->n_views <= gsr::kWideSums;
+  const int blocks = persistent_blocks(c, s, gsr::kBwdHeld);
   gsr::BwdArgs ba{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz, s->Tfin, s->last,
-                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, s->by_length ? s->order : nullptr,
-                  persistent_blocks(c, s, gsr::kBwdHeld),
+                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, item_order(s), blocks,
                   nullptr, nullptr};
   if (s->det) {
     // arena D is in place (ensure_D): list positions of every (record, tile),
@@ -1501,7 +1507,7 @@ int gsr_state_stats(gsr_ctx* c, gsr_state* s, int64_t out[6]) {
   GSR_HIP(c, hipMemsetAsync(c->d_stats, 0, 64, st));
   gsr::FwdArgs fa{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz,
                   nullptr, nullptr, nullptr, nullptr, s->last, c->d_stats,
-                  s->R.n_tiles * s->n_views, nullptr, nullptr, 0};
+                  s->R.n_tiles * s->n_views, nullptr, gsr::ItemOrder{}, 0};
   gsr::launch_render_fwd(s->R, fa, st);
   unsigned long long h[3] = {0, 0, 0};
   GSR_HIP(c, hipMemcpyAsync(h, c->d_stats, sizeof(h), hipMemcpyDeviceToHost, st));

@@ -230,7 +230,7 @@ struct BinArgs {
   uint32_t* M;             // [n_views][n_wg][n_tiles]
   uint32_t* T;             // [n_items] pair totals; zero between launches
   int2* R;                 // [n_items] unclipped ranges
-  int* order;              // [n_items] items from the longest list to the shortest
+  int* order;              // [n_items] items from the longest list to the shortest, if that pays
   uint32_t* ticket;        // zero between launches
   uint32_t* K;             // overlap count
   uint32_t* K_host;        // NULL or a device-visible host word that also receives K
@@ -244,10 +244,29 @@ struct BinArgs {
 // and backward, 320x240 with 31K Gaussians (K about 65,000) 41.8 -> 45.9 us and
 // 84.2 -> 85.7, 560x360 with 81K (170,000) 53.4 -> 55.1 and 112 -> 111, with
 // 242K (390,000) 93.2 -> 92.0 and 207 -> 195, 800x500 with 480K 138 -> 121 and
-// 329 -> 301. The counting pass asks with the exact K and else writes the
-// plain order; a launch asks with the capacity, which is no smaller.
-constexpr int64_t kOrderItems = 512;
-__host__ __device__ __forceinline__ bool order_pays(int64_t n, int64_t K) { return n > kOrderItems && K >= 1 << 18; }
+// 329 -> 301. n is asked where the launch is made, K on the device, where it
+// is known: what a state's workspace has room for says nothing about this call.
+constexpr int kOrderItems = 512;
+constexpr uint32_t kOrderEntries = 1 << 18;
+struct ItemOrder {
+  const int* items;   // NULL = by position
+  const uint32_t* K;  // by length if *K >= least
+  uint32_t least;
+};
+// The item that is taken i-th, where item `at` stands in for it, and its
+// range. K, the order and the range that it may be are read side by side.
+struct Item {
+  int index;
+  int2 range;
+};
+__device__ __forceinline__ Item item_at(const ItemOrder& o, const int2* __restrict__ ranges, int i, int at) {
+  Item r{at, ranges[at]};
+  if (o.items) {
+    const int it = o.items[i];
+    if (*o.K >= o.least) r = Item{it, ranges[it]};
+  }
+  return r;
+}
 // Workgroups per view: 1,024 Gaussians each, at most 128, and over all views at
 // most about one per compute unit. Every workgroup reserves room on every tile
 // it meets, with an atomic on a word that all of the view's workgroups share:
@@ -261,7 +280,7 @@ void launch_bin_count(const Raster& R, const BinArgs& a, hipStream_t s);
 // LDS sort per tile writing ids[cap] (record indices in depth order).
 // scratch: [cap] keys, used by ranges longer than LDS holds.
 void launch_tile_bins(const Raster& R, const BinArgs& a, int64_t n_items, int2* ranges, uint64_t* scratch,
-                      uint32_t* ids, hipStream_t s);
+                      uint32_t* ids, const ItemOrder& order, hipStream_t s);
 
 struct FwdArgs {
   const int2* ranges;
@@ -274,7 +293,7 @@ struct FwdArgs {
   unsigned long long* stats;  // non-NULL: count work only, write no outputs
   int n_items;                // views * tiles; item = view * n_tiles + tile
   int* queue;                 // persistent launch: work counter (zeroed first)
-  const int* order;           // [n_items] the items in the order they are taken (NULL = by position)
+  ItemOrder order;            // the order in which the items are taken
   int blocks;                 // persistent launch: workgroups (0 = one per item)
 };
 void launch_render_fwd(const Raster& R, const FwdArgs& a, hipStream_t s);
@@ -309,7 +328,7 @@ struct BwdArgs {
   bool geom_only;  // only fields 0-4 and 9 are needed (no opacity or colour gradient wanted)
   int n_items;
   int* queue;
-  const int* order;
+  ItemOrder order;
   int blocks;
   // deterministic backward (both NULL otherwise): per (list position,
   // 8x8 block of the tile) sums [K, 4, 10 or 6] and per list position the

@@ -192,8 +192,8 @@ __device__ __forceinline__ void last_totals(const int2* R, int64_t base, int64_t
 // One workgroup: R[i] = (start, start + T[i]) with start the exclusive scan of
 // the tile totals T[0, n) (read at the device-coherent level), T[i] = 0, and
 // order = the items from the longest list to the shortest, by buckets (the
-// order inside a bucket is arbitrary), few items with each round of kUnits
-// reversed; returns the sum. bins: kOrderBuckets words of LDS.
+// order inside a bucket is arbitrary), if that pays (see ItemOrder), few items
+// with each round of kUnits reversed; returns the sum. bins: kOrderBuckets words of LDS.
 // The sort and both compositing passes take the items in that order: a long
 // list that starts last is what a launch of a few items per compute unit ends
 // with, and runs of neighbouring tiles on one XCD, whose shared records its L2
@@ -202,7 +202,7 @@ __device__ __forceinline__ void last_totals(const int2* R, int64_t base, int64_t
 // 1M 138 -> 115 us forward; of 500K 98 -> 89 and 201 -> 185; 801x533 of 200K
 // 46 -> 43 and 93 -> 85; 640x480 of 500K 77.6 -> 66.6 and 119 (the same). The
 // order costs this kernel 1.7 us (25,800 items: 18, as three kernels of its own
-// 55), and reading it each of the three passes some more: see order_pays.
+// 55), and reading it each of the three passes some more: see ItemOrder.
 __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t* bins, int64_t n) {
   __shared__ uint32_t s_wave[kPlaceThreads / 64];
   static_assert(kOrderBuckets <= kPlaceThreads, "one bucket per thread");
@@ -229,11 +229,7 @@ __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t*
     }
     carry += tot;
   }
-  if (!order_pays(n, carry)) {  // few or short lists: as they lie, where a launch may ask for an order
-    if (n > kOrderItems)
-      for (int64_t i = threadIdx.x; i < n; i += kPlaceThreads) order[i] = (int)i;
-    return carry;
-  }
+  if (n <= kOrderItems || carry < kOrderEntries) return carry;  // no launch goes by the order
   constexpr int64_t kStretch = (int64_t)kPlaceThreads * kScanItems;
   for (int64_t b0 = (n - 1) / kStretch * kStretch; b0 >= 0; b0 -= kStretch) {
     const int64_t base = b0 + (int64_t)threadIdx.x * kScanItems;
@@ -492,7 +488,8 @@ __device__ __forceinline__ void wave_sort(const uint64_t* __restrict__ keys, int
 template <bool kLong>
 __global__ __launch_bounds__(kBinThreads) void k_tile_sort(const int2* __restrict__ ranges, int64_t n_items,
                                                           uint64_t* __restrict__ keys, uint64_t* __restrict__ scratch,
-                                                          uint32_t* __restrict__ ids, const int* __restrict__ order) {
+                                                          uint32_t* __restrict__ ids, ItemOrder ord) {
+  const int* order = ord.items && *ord.K >= ord.least ? ord.items : nullptr;
   constexpr int kItems = kBinThreads / 64;
   constexpr int kWaveSort = kLong ? 2048 : 1024, kLongRun = kWaveSort / 2;
   const int w = threadIdx.x >> 6;
@@ -618,15 +615,14 @@ void launch_bin_count(const Raster& R, const BinArgs& a, hipStream_t s) {
 }
 
 void launch_tile_bins(const Raster& R, const BinArgs& a, int64_t n_items, int2* ranges, uint64_t* scratch,
-                      uint32_t* ids, hipStream_t s) {
+                      uint32_t* ids, const ItemOrder& order, hipStream_t s) {
   if (n_items <= 0) return;
   BinArgs b = a;
   b.ranges = ranges;
   hipLaunchKernelGGL(k_bin_place, bin_grid(R, b), dim3(kPlaceThreads), bin_lds(R), s, R, b);
   const auto sort = a.cap > 1024 * n_items ? k_tile_sort<true> : k_tile_sort<false>;
   hipLaunchKernelGGL(sort, dim3((unsigned)((n_items + kBinThreads / 64 - 1) / (kBinThreads / 64))),
-                     dim3(kBinThreads), 0, s, (const int2*)ranges, n_items, a.keys, scratch, ids,
-                     order_pays(n_items, a.cap) ? (const int*)a.order : (const int*)nullptr);
+                     dim3(kBinThreads), 0, s, (const int2*)ranges, n_items, a.keys, scratch, ids, order);
 }
 
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s) {
