@@ -9,9 +9,9 @@
 // start + its offset, and writes the keys (float bits of the camera depth <<
 // 32 | record index) in arbitrary order. Finally each tile's range is sorted
 // by key and its record indices written: by one wave in registers (a bitonic
-// network of up to 1024 or 2048 keys), or for longer ranges by the waves of a
-// workgroup side by side (runs of half as many, merged pairwise in global
-// memory). Keys are unique within a tile, so the result is the depth order of the "m ordered Gaussians" of
+// network of up to 1024 keys), or for longer ranges by a workgroup (runs of 512
+// keys merged in LDS to pieces of 2048, those pairwise in global memory). Keys
+// are unique within a tile, so the result is the depth order of the "m ordered Gaussians" of
 // Eq. 3 and Eq. 6 with ties broken by index: exactly what a stable sort of
 // (tile, depth) gives. No launch grid depends on K: positions at or beyond
 // the capacity are dropped and flagged, so the same launches serve captured
@@ -416,20 +416,19 @@ __device__ __forceinline__ uint64_t lane_xor64(uint64_t v, int m) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// Sorts keys[b, b + len) (0 < len <= 64 E) with one wave: lane l holds
+// Sorts keys[0, len) (0 < len <= 64 E) with one wave: lane l holds
 // elements E l .. E l + E - 1 in registers; a bitonic network whose strides
 // below E are compare-exchanges inside a lane and whose larger strides
-// exchange with lane l ^ (stride / E). Writes the low words (record indices)
-// to ids (kKeys false) or the sorted keys to out_keys[b, b + len) (kKeys true).
-template <int E, bool kKeys = false>
-__device__ __forceinline__ void wave_sort(const uint64_t* __restrict__ keys, int64_t b, int len,
-                                          uint32_t* __restrict__ ids, uint64_t* __restrict__ out_keys = nullptr) {
-  const int lane = threadIdx.x & 63;
+// exchange with lane l ^ (stride / E). put(i, key) takes the i-th smallest.
+template <int E, class Put>
+__device__ __forceinline__ void wave_sort(const uint64_t* __restrict__ keys, int len, Put put) {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));  // what follows from it is worked out here, and not kept in registers around a loop
   uint64_t e[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const int i = kWave * r + lane;  // any order will do to begin with: whole lines
-    e[r] = i < len ? keys[b + i] : ~0ull;  // padding sorts last (keys hold finite depths)
+    e[r] = i < len ? keys[i] : ~0ull;  // padding sorts last (keys hold finite depths)
   }
 #pragma unroll
   for (int k = 2; k <= 64 * E; k <<= 1) {
@@ -465,86 +464,132 @@ __device__ __forceinline__ void wave_sort(const uint64_t* __restrict__ keys, int
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const int i = E * lane + r;
-    if (i < len) {
-      if (kKeys) out_keys[b + i] = e[r];
-      else ids[b + i] = (uint32_t)e[r];
-    }
+    if (i < len) put(i, e[r]);
   }
 }
 
-// Four (view, tile) items per workgroup. Each wave sorts one item of at most
-// kWaveSort keys in registers (the smallest of the 256 / 512 / 1024 / 2048-key
-// networks that holds it). Longer items are cut into runs of kLongRun keys,
-// which the workgroup's waves sort side by side into scratch, and pairwise
-// merges (ping-pong between scratch and keys) join.
-// Bound by the longest item's chain of exchanges. The 2048-key network takes 49
-// us, and its 133 registers (71 without it) leave three waves a SIMD to every
-// list; it serves a few long lists badly: 1200x680 of 1M (14 of 3,225 lists of
-// 1025 to 1075 keys) 49 -> 38 us with those in runs of 512, 8 views of it 112
-// -> 65. Where most lists are that long, a workgroup's merges one after the
-// other are worse (nine lists of 2000 keys 45 -> 78 us): kLong, up to 2048 keys
-// and runs of 1024, is for mean lengths above 1024. The 256-key network: lists
-// of 140 keys 9.6 -> 5.5 us. The keys are read in whole lines (38.4 against 39.0).
-template <bool kLong>
-__global__ __launch_bounds__(kBinThreads) void k_tile_sort(const int2* __restrict__ ranges, int64_t n_items,
+// A piece of up to kPiece keys of a long list in LDS, sorted by a workgroup:
+// its waves sort runs of kRun keys in registers, two rounds of merges join them.
+constexpr int kRun = 512, kPiece = kRun * (kBinThreads / 64);
+constexpr int kPerThread = kPiece / kBinThreads;
+// The place of key i: threads reading the same key of their shares of eight
+// would meet in four of the 32 pairs of banks; so they meet in all.
+__device__ __forceinline__ int piece_at(int i) { return i ^ ((i >> 5) & (kPerThread - 1)); }
+
+// Merges the neighbouring sorted runs of wd keys (the last one may be shorter
+// or missing) of the piece's len keys. Thread t takes keys kPerThread t and up
+// of the result, which lie in one pair of runs, from where its merge path
+// crosses them; put(i, key) takes the i-th.
+template <class Put>
+__device__ __forceinline__ void merge_round(const uint64_t* piece, int len, int wd, Put put) {
+  int first = (int)threadIdx.x * kPerThread;
+  asm volatile("" : "+v"(first));  // (as in wave_sort)
+  const int lo = first & ~(2 * wd - 1), mid = min(lo + wd, len), hi = min(lo + 2 * wd, len);
+  const int na = mid - lo, nb = hi - mid, d0 = first - lo;
+  int i0 = max(0, d0 - nb), i1 = min(d0, na);
+  while (i0 < i1) {  // the first i with a[i] > b[d0 - 1 - i]
+    const int m = (i0 + i1) >> 1;
+    if (piece[piece_at(lo + m)] < piece[piece_at(mid + d0 - 1 - m)]) i0 = m + 1;
+    else i1 = m;
+  }
+  int i = lo + i0, j = mid + d0 - i0;
+  // (a run that has ended reads as the largest key, which no list holds: its depth is NaN)
+  uint64_t a = i < mid ? piece[piece_at(i)] : ~0ull, b = j < hi ? piece[piece_at(j)] : ~0ull;
+#pragma unroll
+  for (int k = 0; k < kPerThread; ++k) {
+    const bool take_a = a < b;
+    const uint64_t key = take_a ? a : b;
+    if (first + k < hi) put(k, key);
+    if (take_a) a = ++i < mid ? piece[piece_at(i)] : ~0ull;
+    else b = ++j < hi ? piece[piece_at(j)] : ~0ull;
+  }
+}
+
+// Sorts keys[0, len) (0 < len <= kPiece) with the whole workgroup; put(i, key)
+// takes the i-th smallest. Ends with the piece free for the next one.
+template <class Put>
+__device__ __forceinline__ void piece_sort(const uint64_t* __restrict__ keys, int len, uint64_t* piece, Put put) {
+  const int c0 = kRun * (int)(threadIdx.x >> 6);
+  if (c0 < len)
+    wave_sort<kRun / 64>(keys + c0, min(kRun, len - c0), [&](int i, uint64_t key) { piece[piece_at(c0 + i)] = key; });
+  __syncthreads();
+  int first = (int)threadIdx.x * kPerThread;
+  asm volatile("" : "+v"(first));  // (as in wave_sort)
+  if (len > 2 * kRun) {
+    uint64_t out[kPerThread];
+    if (first < len) merge_round(piece, len, kRun, [&](int k, uint64_t key) { out[k] = key; });
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k)
+      if (first + k < len) piece[piece_at(first + k)] = out[k];
+    __syncthreads();
+    if (first < len) merge_round(piece, len, 2 * kRun, [&](int k, uint64_t key) { put(first + k, key); });
+  } else if (first < len) {
+    merge_round(piece, len, kRun, [&](int k, uint64_t key) { put(first + k, key); });
+  }
+  __syncthreads();
+}
+
+// `per` (view, tile) items per workgroup, one for each wave or one in all.
+// Each wave sorts an item of at most kWaveSort keys in registers (the smallest
+// of the 256 / 512 / 1024-key networks that holds it). A longer item the whole
+// workgroup sorts: up to kPiece keys in LDS, beyond that in pieces of as many,
+// which pairwise merges (ping-pong between scratch and keys) join.
+// Bound by the longest item's chain of exchanges. No kernel is chosen by how
+// long the lists may be: the launch does not know it. What the choices would
+// be, with placement, us (a 2048-key network in registers, whose 133 registers
+// leave three waves a SIMD to every list | runs of 512 merged in global memory
+// | here): 3,225 lists of 300, none longer 34 | 31 | 32, 13 of 2000 among them
+// 55 | 44 | 37, half of 1500 103 | 108 | 88, all of 2000 207 | 258 | 174; 1,200
+// lists, 120 of 1100 among 300s 45 | 33 | 22, all of 2000 89 | 135 | 62; one
+// list of 16000 245 | 290 | 233. 8 views of 1200x680, 1M: 112 | 64 | 69 without
+// placement, as the 16 KB of LDS are held until a workgroup's last wave ends.
+__global__ __launch_bounds__(kBinThreads) void k_tile_sort(const int2* __restrict__ ranges, int n_items, int per,
                                                           uint64_t* __restrict__ keys, uint64_t* __restrict__ scratch,
                                                           uint32_t* __restrict__ ids, ItemOrder ord) {
-  const int* order = ord.items && *ord.K >= ord.least ? ord.items : nullptr;
-  constexpr int kItems = kBinThreads / 64;
-  constexpr int kWaveSort = kLong ? 2048 : 1024, kLongRun = kWaveSort / 2;
-  const int w = threadIdx.x >> 6;
-  // the workgroup's it-th item: four neighbours, or with an order one of each
-  // quarter of it, so that no workgroup gets several of the longest (25,800
-  // lists, 138 -> 103 us)
-  auto at = [&](int it) {
-    return order ? (int64_t)blockIdx.x + (int64_t)it * gridDim.x : (int64_t)blockIdx.x * kItems + it;
+  __shared__ uint64_t piece[kPiece];
+  constexpr int kItems = kBinThreads / 64, kWaveSort = 1024;
+  static_assert(kItems == 4, "four lanes hold the items' ranges");
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  // The workgroup's items: neighbours, or by length one of each part of the
+  // order, so that no workgroup gets several of the longest (25,800 lists, 135
+  // -> 69 us).
+  int2 rg;  // lane it (modulo four): the it-th item's range
+  {
+    const int it = threadIdx.x & 3;
+    const int i = (int)blockIdx.x + it * (int)gridDim.x, p = (int)blockIdx.x * per + it;
+    const bool by_length = ord.items && *ord.K >= ord.least;
+    rg = item_at(ord, ranges, min(i, n_items - 1), min(p, n_items - 1)).range;
+    if (it >= per || (by_length ? i : p) >= n_items) rg = make_int2(0, 0);
+  }
+  auto pick = [&](int it) {
+    return make_int2(__builtin_amdgcn_readlane(rg.x, it), __builtin_amdgcn_readlane(rg.y, it));
   };
-  auto range = [&](int it) { return ranges[order ? order[at(it)] : at(it)]; };
-  if (at(w) < n_items) {
-    const int2 rg = range(w);
-    const int len = rg.y - rg.x;
-    if (len > 0 && len <= 256) {
-      wave_sort<4>(keys, rg.x, len, ids);
-    } else if (len > 256 && len <= 512) {
-      wave_sort<8>(keys, rg.x, len, ids);
-    } else if (len > 512 && len <= 1024) {
-      wave_sort<16>(keys, rg.x, len, ids);
-    } else if (kLong && len > 1024 && len <= kWaveSort) {
-      wave_sort<kLong ? 32 : 16>(keys, rg.x, len, ids);
-    }
+  {
+    const int2 own = pick(w);
+    const int len = own.y - own.x;
+    auto put = [&](int i, uint64_t key) { ids[own.x + i] = (uint32_t)key; };
+    if (len > 0 && len <= 256) wave_sort<4>(keys + own.x, len, put);
+    else if (len > 256 && len <= 512) wave_sort<8>(keys + own.x, len, put);
+    else if (len > 512 && len <= kWaveSort) wave_sort<16>(keys + own.x, len, put);
   }
-  // runs of the long items, dealt to the waves in turn
-  int n_runs = 0;
-  for (int it = 0; it < kItems && at(it) < n_items; ++it) {
-    const int2 rg = range(it);
-    const int len = rg.y - rg.x;
-    if (len > kWaveSort) n_runs += (len + kLongRun - 1) / kLongRun;
-  }
-  if (n_runs == 0) return;  // uniform across the workgroup
-  for (int j = w; j < n_runs; j += kItems) {
-    int r = j;
-    for (int it = 0; it < kItems && at(it) < n_items; ++it) {
-      const int2 rg = range(it);
-      const int len = rg.y - rg.x;
-      const int nr = len > kWaveSort ? (len + kLongRun - 1) / kLongRun : 0;
-      if (r < nr) {
-        const int c0 = r * kLongRun;
-        wave_sort<kLongRun / 64, true>(keys, rg.x + c0, min(kLongRun, len - c0), nullptr, scratch);
-        break;
-      }
-      r -= nr;
-    }
-  }
-  __threadfence_block();
-  __syncthreads();
-  for (int it = 0; it < kItems && at(it) < n_items; ++it) {
-    const int2 rg = range(it);
-    const int64_t b = rg.x;
-    const int len = rg.y - rg.x;
+#pragma unroll 1
+  for (int it = 0; it < per; ++it) {
+    const int2 r = pick(it);
+    const int64_t b = r.x;
+    const int len = r.y - r.x;
     if (len <= kWaveSort) continue;  // uniform across the workgroup
+    for (int c0 = 0; c0 < len; c0 += kPiece)
+      piece_sort(keys + b + c0, min(kPiece, len - c0), piece, [&](int i, uint64_t key) {
+        if (len <= kPiece) ids[b + i] = (uint32_t)key;
+        else scratch[b + c0 + i] = key;
+      });
+    if (len <= kPiece) continue;
+    __threadfence_block();
+    __syncthreads();
     uint64_t* src = scratch + b;
     uint64_t* dst = keys + b;
-    for (int wd = kLongRun; wd < len; wd <<= 1) {
+    for (int wd = kPiece; wd < len; wd <<= 1) {
       for (int lo = 0; lo < len; lo += 2 * wd) {
         const int mid = min(lo + wd, len), hi = min(lo + 2 * wd, len);
         merge_runs(src + lo, mid - lo, src + mid, hi - mid, dst + lo);
@@ -620,9 +665,13 @@ void launch_tile_bins(const Raster& R, const BinArgs& a, int64_t n_items, int2* 
   BinArgs b = a;
   b.ranges = ranges;
   hipLaunchKernelGGL(k_bin_place, bin_grid(R, b), dim3(kPlaceThreads), bin_lds(R), s, R, b);
-  const auto sort = a.cap > 1024 * n_items ? k_tile_sort<true> : k_tile_sort<false>;
-  hipLaunchKernelGGL(sort, dim3((unsigned)((n_items + kBinThreads / 64 - 1) / (kBinThreads / 64))),
-                     dim3(kBinThreads), 0, s, (const int2*)ranges, n_items, a.keys, scratch, ids, order);
+  // Few items: a workgroup for each, so that all four waves share a long one
+  // (1,200 lists, all of 1100 keys 73 -> 40 us with placement, of 300 the same);
+  // beyond what the chip holds at a time, one for each wave (3,225 lists of 300
+  // 37 -> 32 us, 25,800 187 -> 160).
+  const int per = n_items <= kHeldRounds * kUnits ? 1 : kBinThreads / 64;
+  hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)((n_items + per - 1) / per)),
+                     dim3(kBinThreads), 0, s, (const int2*)ranges, (int)n_items, per, a.keys, scratch, ids, order);
 }
 
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s) {
