@@ -130,10 +130,11 @@ int gsr_render_fwd(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *cam, 
  * is optimised against all its keyframes, Sec. 3.2). poses7: device [V,7];
  * outputs color [V,3,H,W], depth [V,H,W], alpha [V,H,W]. All views' (tile,
  * depth) keys are sorted together and every (view, tile) item is composited
- * by ONE launch, longest tile list first: with blocks_per_cu > 0 a persistent
- * grid of blocks_per_cu x (compute units) workgroups takes items from a work
- * counter, unless the chip could not hold more workgroups than that; with 0,
- * one workgroup per item. gsr_render_fwd is the V = 1,
+ * by ONE launch: with blocks_per_cu > 0 a persistent grid of blocks_per_cu x
+ * (compute units) workgroups takes items from a work counter, longest tile
+ * list first; with 0, or with as many as the chip holds at a time (6 forward,
+ * 5 backward), one workgroup per item, longest first where the lists are many
+ * and long enough for that to pay. gsr_render_fwd is the V = 1,
  * blocks_per_cu = 0 case. Synchronises once (overlap count). */
 int gsr_render_fwd_batch(gsr_ctx *ctx, const gsr_gaussians *g, int32_t n_views, const gsr_camera *cam,
                          const gsr_opts *opts, int32_t blocks_per_cu, const float *poses7, float *color,

@@ -461,19 +461,24 @@ struct Stage {
   }
 };
 
-gsr::BinArgs bin_args(gsr_state* s, int64_t cap, uint32_t* K_host = nullptr) {
-  return gsr::BinArgs{s->n,     s->n_views, s->n_wg, s->rect, s->bin_M,    s->bin_T,       s->bin_R,
-                      s->order, s->bin_ticket, s->d_K, K_host, cap, s->keys, s->d_overflow};
-}
-
 // The persistent grid of a compositing pass of which a compute unit holds
 // `held` workgroups; 0: one workgroup per item.
 int persistent_blocks(const gsr_ctx* c, const gsr_state* s, int held) {
   return s->blocks < held * c->n_cu ? s->blocks : 0;
 }
 
-// The order in which the passes take the items.
-gsr::ItemOrder item_order(const gsr_state* s) {
+gsr::BinArgs bin_args(const gsr_ctx* c, gsr_state* s, int64_t cap, uint32_t* K_host = nullptr) {
+  // (a persistent backward comes only with a persistent forward)
+  static_assert(gsr::kBwdHeld <= gsr::kFwdHeld, "the order is made for both passes");
+  const bool always = persistent_blocks(c, s, gsr::kFwdHeld) > 0;
+  return gsr::BinArgs{s->n,     s->n_views, s->n_wg,       s->rect, s->bin_M, s->bin_T, s->bin_R, s->order,
+                      always,   s->bin_ticket, s->d_K, K_host, cap, s->keys, s->d_overflow};
+}
+
+// The order in which a pass takes the items, for a grid of `blocks` persistent
+// workgroups or (0) one per item.
+gsr::ItemOrder item_order(const gsr_state* s, int blocks) {
+  if (blocks > 0) return {s->order, s->d_K, 0};
   return {s->R.n_tiles * s->n_views > gsr::kOrderItems ? s->order : nullptr, s->d_K, gsr::kOrderEntries};
 }
 
@@ -489,7 +494,7 @@ void enqueue_front(gsr_ctx* c, gsr_state* s, hipStream_t st, uint32_t* K_host = 
   {
     Stage t(c, "bin_count");
     s->n_wg = gsr::bin_workgroups(s->n, s->n_views);
-    gsr::launch_bin_count(s->R, bin_args(s, 0, K_host), st);
+    gsr::launch_bin_count(s->R, bin_args(c, s, 0, K_host), st);
   }
 }
 
@@ -501,10 +506,10 @@ void enqueue_back(gsr_ctx* c, gsr_state* s, hipStream_t st, int64_t cap, float* 
   const gsr::Raster& R = s->R;
   const int n_items = R.n_tiles * s->n_views;
   const int blocks = persistent_blocks(c, s, gsr::kFwdHeld);
-  const gsr::ItemOrder order = item_order(s);
+  const gsr::ItemOrder order = item_order(s, blocks);
   {
     Stage t(c, "tile_bins");
-    gsr::launch_tile_bins(R, bin_args(s, cap), n_items, s->ranges, s->scratch, s->ids, order, st);
+    gsr::launch_tile_bins(R, bin_args(c, s, cap), n_items, s->ranges, s->scratch, s->ids, order, st);
   }
   gsr::FwdArgs fa{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz,
                   color, depth, alpha, s->Tfin, s->last, nullptr,
@@ -528,7 +533,7 @@ void enqueue_bwd(gsr_ctx* c, gsr_state* s, hipStream_t st, const float* gC, cons
   const bool wide = !s->det && s->n * s->n_views <= gsr::kWideSums;
   const int blocks = persistent_blocks(c, s, gsr::kBwdHeld);
   gsr::BwdArgs ba{s->ranges, s->ids, s->rec_uvab, s->rec_cob, s->rec_rgbz, s->Tfin, s->last,
-                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, item_order(s), blocks,
+                  gC, gD, gA, s->g2d, wide, geom_only, n_items, s->queue, item_order(s, blocks), blocks,
                   nullptr, nullptr};
   if (s->det) {
     // arena D is in place (ensure_D): list positions of every (record, tile),

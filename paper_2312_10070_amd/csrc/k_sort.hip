@@ -193,7 +193,8 @@ __device__ __forceinline__ void last_totals(const int2* R, int64_t base, int64_t
 // the tile totals T[0, n) (read at the device-coherent level), T[i] = 0, and
 // order = the items from the longest list to the shortest, by buckets (the
 // order inside a bucket is arbitrary), if that pays (see ItemOrder), few items
-// with each round of kUnits reversed; returns the sum. bins: kOrderBuckets words of LDS.
+// with each round of kUnits reversed; or in any case, and none reversed
+// (kAlways). Returns the sum. bins: kOrderBuckets words of LDS.
 // The sort and both compositing passes take the items in that order: a long
 // list that starts last is what a launch of a few items per compute unit ends
 // with, and runs of neighbouring tiles on one XCD, whose shared records its L2
@@ -203,6 +204,7 @@ __device__ __forceinline__ void last_totals(const int2* R, int64_t base, int64_t
 // 46 -> 43 and 93 -> 85; 640x480 of 500K 77.6 -> 66.6 and 119 (the same). The
 // order costs this kernel 1.7 us (25,800 items: 18, as three kernels of its own
 // 55), and reading it each of the three passes some more: see ItemOrder.
+template <bool kAlways>
 __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t* bins, int64_t n) {
   __shared__ uint32_t s_wave[kPlaceThreads / 64];
   static_assert(kOrderBuckets <= kPlaceThreads, "one bucket per thread");
@@ -229,7 +231,7 @@ __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t*
     }
     carry += tot;
   }
-  if (n <= kOrderItems || carry < kOrderEntries) return carry;  // no launch goes by the order
+  if (!kAlways && (n <= kOrderItems || carry < kOrderEntries)) return carry;  // no launch goes by the order
   constexpr int64_t kStretch = (int64_t)kPlaceThreads * kScanItems;
   for (int64_t b0 = (n - 1) / kStretch * kStretch; b0 >= 0; b0 -= kStretch) {
     const int64_t base = b0 + (int64_t)threadIdx.x * kScanItems;
@@ -251,7 +253,7 @@ __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t*
     for (int i = 0; i < kScanItems; ++i)
       if (base + i < n) {
         uint32_t p = atomicAdd(&bins[order_bucket(v[i])], 1u);
-        if (n <= kHeldRounds * kUnits && (int64_t)((p | (kUnits - 1)) + 1) <= n) p ^= kUnits - 1;
+        if (!kAlways && n <= kHeldRounds * kUnits && (int64_t)((p | (kUnits - 1)) + 1) <= n) p ^= kUnits - 1;
         order[p] = (int)(base + i);
       }
   }
@@ -262,6 +264,7 @@ __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t*
 // workgroup w's pairs inside the range of tile t of view v (reserved with an
 // atomic on T, so the order of the workgroups inside a tile is arbitrary).
 // The last workgroup writes the ranges R, the item order and K.
+template <bool kAlways>
 __global__ __launch_bounds__(kPlaceThreads) void k_bin_count(Raster Rr, BinArgs a) {
   extern __shared__ uint32_t hist[];
   __shared__ bool last;
@@ -309,7 +312,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_bin_count(Raster Rr, BinArgs 
   }
   __syncthreads();
   if (!last) return;
-  const uint32_t K = scan_tile_totals(a.T, a.R, a.order, hist, (int64_t)Rr.n_tiles * a.n_views);
+  const uint32_t K = scan_tile_totals<kAlways>(a.T, a.R, a.order, hist, (int64_t)Rr.n_tiles * a.n_views);
   if (threadIdx.x == 0) {
     *a.K = K;
     if (a.K_host) *a.K_host = K;
@@ -656,7 +659,7 @@ void launch_bin_count(const Raster& R, const BinArgs& a, hipStream_t s) {
     if (a.K_host) launch_fill_u32(a.K_host, 0u, 1, s);
     return;
   }
-  hipLaunchKernelGGL(k_bin_count, bin_grid(R, a), dim3(kPlaceThreads), bin_lds(R), s, R, a);
+  hipLaunchKernelGGL(a.order_always ? k_bin_count<true> : k_bin_count<false>, bin_grid(R, a), dim3(kPlaceThreads), bin_lds(R), s, R, a);
 }
 
 void launch_tile_bins(const Raster& R, const BinArgs& a, int64_t n_items, int2* ranges, uint64_t* scratch,

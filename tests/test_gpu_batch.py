@@ -106,3 +106,30 @@ def test_autotune_picks_a_timed_configuration():
     assert (best.tile_w, best.tile_h) in ((16, 16), (8, 32), (32, 8)) and bpc in (0, 1, 2, 4, 8)
     assert all(t > 0 for t in table.values())
     assert table[(best.tile_w, best.tile_h, bpc)] == min(table.values())
+
+
+def test_persistent_grid_takes_the_longest_list_first():
+    """500 lists on a persistent grid of 256 workgroups, one of them twice as
+    long as the others, in the first tile or in the last. Taken first in both,
+    it is walked beside the others; taken where it lies, it would follow others
+    in the second (1.4 times the first's time)."""
+    torch = torch_()
+    from tests.test_gpu_sort import frame
+
+    def stage(long_at):
+        lengths = np.full(500, 1500)
+        lengths[long_at] = 3000
+        g, pose, cam, _, _ = frame(25, 20, lengths)
+        got = []
+        for _ in range(12):
+            gsr.profile_enable(True)
+            gsr.render_fwd_batch(*g, pose[None], cam, blocks_per_cu=1)[3].release()
+            torch.cuda.synchronize()
+            gsr.profile_enable(False)
+            ms, calls = gsr.profile_read()["render_fwd"]
+            got.append(ms / calls)
+        return min(got)
+
+    first, last = stage(0), stage(499)
+    print(f"forward: {1e3 * first:.1f} us with the long list first, {1e3 * last:.1f} us last")
+    assert last < 1.2 * first
