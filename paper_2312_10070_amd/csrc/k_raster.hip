@@ -409,7 +409,7 @@ __device__ __forceinline__ int g2d_field6(int f) { return f < 5 ? f : 9; }
 // Per-pixel state of the backward: the forward's final transmittance and last
 // composited position, the upstream gradients, and the running suffix term.
 struct BwdPix {
-  float T, g0, g1, g2, gd, gS;
+  float T, g0, g1, g2, gd, gS, gA;
   int last;
 };
 
@@ -418,7 +418,7 @@ struct BwdPix {
 // sum_{u > j} z_u alpha_u T_u (depth), g = (gC, gD). Only the dot product
 // gS = g . S_j is needed; the background enters it through T_fin bg.
 __device__ __forceinline__ BwdPix bwd_pixel(const Raster& Rr, const BwdArgs& a, const Pixel& q) {
-  BwdPix b{1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0};
+  BwdPix b{1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0};
   float ga = 0.f;
   if (q.inside) {
     const int64_t P = (int64_t)Rr.W * Rr.H;
@@ -432,7 +432,8 @@ __device__ __forceinline__ BwdPix bwd_pixel(const Raster& Rr, const BwdArgs& a, 
     b.gd = a.gD[p];
     ga = a.gA ? a.gA[p] : 0.f;
   }
-  b.gS = b.T * (b.g0 * Rr.bg0 + b.g1 * Rr.bg1 + b.g2 * Rr.bg2) - ga * b.T;
+  b.gS = b.T * (b.g0 * Rr.bg0 + b.g1 * Rr.bg1 + b.g2 * Rr.bg2);
+  b.gA = ga * b.T;
   return b;
 }
 
@@ -483,7 +484,13 @@ __device__ __forceinline__ BwdPix bwd_pixel(const Raster& Rr, const BwdArgs& a, 
 // the record, block of the tile) and the block's bit set in a.mask instead; a
 // later pass adds them per Gaussian in a fixed order, so the result does not
 // depend on the order waves run in.
-template <int NF, BwdSums SUMS>
+//
+// ALPHA: with an upstream gradient of alpha. Its term gA = dL/dA T_fin is
+// subtracted from the suffix sum per pair: folded into the sum from the start,
+// as it may be for nothing, it had every addition rounded to its size (an alpha
+// gradient a thousand times the colour's, 200 layers: dL/do off by 2.1e-7 rms,
+// so 6.0e-8). A kernel of its own, as the operation costs the others 3 %.
+template <int NF, BwdSums SUMS, bool ALPHA>
 __device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, const Item& item, BwdWave* smem) {
   constexpr int H = NF / 2;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -581,7 +588,7 @@ __device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, con
         const float inv = __builtin_amdgcn_rcpf(1.f - al);  // 1 ulp; alpha <= alpha_max < 1
         const float Tj = b.T * inv;
         const float wt = al * Tj;
-        const float dA = fmaf(Tj, gc[s], -inv * b.gS);
+        const float dA = fmaf(Tj, gc[s], -inv * (ALPHA ? b.gS - b.gA : b.gS));
         b.gS = fmaf(gc[s], wt, b.gS);
         b.T = Tj;
         // a clamped alpha does not depend on o or sigma
@@ -657,11 +664,11 @@ __global__ __launch_bounds__(kTileThreads) void k_render_fwd(Raster Rr, FwdArgs 
   fwd_item<STATS>(Rr, a, item_at(a.order, a.ranges, b, xcd_tile(b, (int)gridDim.x)), sm);
 }
 
-template <int NF, BwdSums SUMS>
+template <int NF, BwdSums SUMS, bool ALPHA>
 __global__ __launch_bounds__(kTileThreads, 5) void k_render_bwd(Raster Rr, BwdArgs a) {
   __shared__ BwdWave sm[kWavesPerTile];
   const int b = (int)blockIdx.x;
-  bwd_item<NF, SUMS>(Rr, a, item_at(a.order, a.ranges, b, xcd_chunk(b, (int)gridDim.x)), sm);
+  bwd_item<NF, SUMS, ALPHA>(Rr, a, item_at(a.order, a.ranges, b, xcd_chunk(b, (int)gridDim.x)), sm);
 }
 
 // Persistent workgroups: take the next item from the queue until it is empty.
@@ -690,7 +697,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void k_render_bwd_persistent(Raste
   __shared__ BwdWave sm[kWavesPerTile];
   __shared__ int s_item;
   Item item;
-  while (next_item(a, &s_item, item)) bwd_item<NF, SUMS>(Rr, a, item, sm);
+  while (next_item(a, &s_item, item)) bwd_item<NF, SUMS, true>(Rr, a, item, sm);
 }
 
 // Deterministic backward, before the compositing pass: rev[goff[o] + j] =
@@ -781,20 +788,22 @@ void launch_render_bwd(const Raster& R, const BwdArgs& a, hipStream_t s) {
   const bool queue = a.blocks > 0;
   const dim3 grid((unsigned)(queue ? a.blocks : a.n_items));
   if (queue) launch_fill_u32(reinterpret_cast<uint32_t*>(a.queue), 0u, 1, s);
-  auto go = [&](auto one, auto many) {
+  auto go = [&](auto plain, auto alpha, auto many) {
     if (queue) hipLaunchKernelGGL(many, grid, tb, 0, s, R, a);
-    else hipLaunchKernelGGL(one, grid, tb, 0, s, R, a);
+    else hipLaunchKernelGGL(a.gA ? alpha : plain, grid, tb, 0, s, R, a);
   };
+#define GSR_BWD(NF, SUMS) k_render_bwd<NF, SUMS, false>, k_render_bwd<NF, SUMS, true>, k_render_bwd_persistent<NF, SUMS>
   // ten fields, or the six of a pose-only backward
   if (a.geom_only) {
-    if (det) go(k_render_bwd<6, kStored>, k_render_bwd_persistent<6, kStored>);
-    else if (a.wide) go(k_render_bwd<6, kWide>, k_render_bwd_persistent<6, kWide>);
-    else go(k_render_bwd<6, kFloat>, k_render_bwd_persistent<6, kFloat>);
+    if (det) go(GSR_BWD(6, kStored));
+    else if (a.wide) go(GSR_BWD(6, kWide));
+    else go(GSR_BWD(6, kFloat));
   } else {
-    if (det) go(k_render_bwd<10, kStored>, k_render_bwd_persistent<10, kStored>);
-    else if (a.wide) go(k_render_bwd<10, kWide>, k_render_bwd_persistent<10, kWide>);
-    else go(k_render_bwd<10, kFloat>, k_render_bwd_persistent<10, kFloat>);
+    if (det) go(GSR_BWD(10, kStored));
+    else if (a.wide) go(GSR_BWD(10, kWide));
+    else go(GSR_BWD(10, kFloat));
   }
+#undef GSR_BWD
 }
 
 void launch_det_rev(const Raster& R, const int2* ranges, const uint32_t* ids, const int4* rect, const uint32_t* goff,

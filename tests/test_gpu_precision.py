@@ -62,3 +62,42 @@ def test_moments_of_small_gaussians():
         err = (got - (q * w).sum((1, 2))) / (q * np.abs(w)).sum((1, 2))
         print(f"sum of q {name}: rms {rms(err):.2e}, largest {np.abs(err).max():.2e}")
         assert rms(err) <= 3 * 2.0 ** -24, name
+
+
+def test_opacities_below_an_alpha_gradient():
+    """200 layers that fill the image, alpha of each its opacity exactly, with an
+    upstream gradient of alpha a thousand times that of colour: the term of what
+    lies behind a layer is small beside the alpha term, and is not to be rounded
+    to its size at every layer.
+
+    The alpha term takes a difference, a reciprocal (1 ulp, twice a rounding), a
+    product, a sum, and the opacity factor: below 2 * 2^-24, rms over layers."""
+    import torch
+    errs = []
+    for seed in range(10):
+        rng = np.random.default_rng(seed)
+        n, W = 200, 16
+        o = rng.integers(270, 400, n) / 65536.0  # (1 - o exact)
+        col = np.zeros((n, 3))
+        col[:, 0] = rng.uniform(0.5, 1, n).astype(np.float32)
+        z = 1 + 0.001 * np.arange(n)
+        g = dev(np.stack([0 * z, 0 * z, z], 1), np.full((n, 3), 1e6), np.tile([1.0, 0, 0, 0], (n, 1)), o, col)
+        cam = gsr.make_camera(W, W, 64.0, 64.0, 8.0, 8.0, 0.2, (0.0, 0.0, 1.0))
+        color, _, _, st = gsr.render_fwd(*g, eye(), cam)
+        T = float(color[2, 3, 3])  # the final transmittance: the third channel is background alone
+        assert bool((color[2] == T).all()) and 0.3 < T < 0.5
+        w = float(np.float32(1e-3))
+        gC = torch.zeros_like(color)
+        gC[0] = w
+        out = gsr.render_bwd(st, gC, torch.zeros((W, W), device="cuda"), torch.ones((W, W), device="cuda"))
+        got = out["opacities"].double().cpu().numpy() / (W * W)
+        st.release()
+        want, behind, t = np.empty(n), 0.0, T
+        for j in range(n - 1, -1, -1):
+            t /= 1 - o[j]
+            want[j] = t * w * col[j, 0] - (behind - T) / (1 - o[j])
+            behind += w * col[j, 0] * o[j] * t
+        errs.append((got - want) / want)
+    err = np.concatenate(errs)
+    print(f"dL/do: rms {rms(err):.2e}, largest {np.abs(err).max():.2e}")
+    assert rms(err) <= 2 * 2.0 ** -24
