@@ -328,7 +328,7 @@ struct BwdArgs {
   const float* Tfin;
   const int* last;
   const float *gC, *gD, *gA;
-  float* g2d;  // [V*n, 10] floats, or doubles if `wide`: sums of q (dx, dy, dx^2, dx dy, dy^2, 1), q = dL/dp / ln 2; r, g, b, z
+  float* g2d;  // [V*n, 10] floats, or doubles if `wide`: sums of q (dx, dy, dx^2, dx dy, dy^2, 1), q = dL/do; r, g, b, z
   bool wide;       // see kWideSums
   bool geom_only;  // only fields 0-4 and 9 are needed (no opacity or colour gradient wanted)
   int n_items;

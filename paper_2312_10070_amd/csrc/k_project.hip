@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256) void k_project(Raster Rr, ProjectArgs a) {
   a.counts[o] = count;
 }
 
-// Backward of the projection for one (Gaussian, view). g2d holds the ten
+// Backward of the projection for one (Gaussian, view). G2 holds the ten
 // per-Gaussian sums of the compositing backward (see below for the first five;
 // then dL/d(o, r, g, b) and the direct dL/dz). Adds to
 // the parameter gradients and returns the pose partials (dL/dR_p, dL/dt).
@@ -188,18 +188,20 @@ __device__ __forceinline__ void chain_one(const Raster& Rr, const PoseF& P, cons
   if (!project_geo(Rr, P, a.means, a.scales, a.quats, k, g)) return;
   const float idet = 1.f / g.det;
   const float A00 = g.Syy * idet, A01 = -g.Sxy * idet, A11 = g.Sxx * idet;
-  // The compositing backward accumulates q = (dL/dalpha) alpha = (dL/dp) / ln 2
-  // per pair, with alpha = o 2^p, p = pa dx^2 + pb dx dy + pc dy^2, dx = px - u
-  // and the stored (pa, pb, pc) = -log2(e) (a/2, b, c/2) of the conic (a, b, c):
-  // G2[0..4] = sum q (dx, dy, dx^2, dx dy, dy^2). As pa, pb, pc are constant per
-  // Gaussian, dL/du = -ln2 (2 pa G2[0] + pb G2[1]) = a G2[0] + b G2[1] (likewise
-  // for v) and dL/da = -ln2 log2(e) G2[2] / 2 = -G2[2] / 2, dL/db = -G2[3].
-  const float g_u = A00 * G2[0] + A01 * G2[1];
-  const float g_v = A01 * G2[0] + A11 * G2[1];
-  const float g_a = -0.5f * G2[2];
-  const float g_b = -G2[3];
-  const float g_c = -0.5f * G2[4];
-  go += G2[5];  // sum q; divided by the opacity below (alpha = o 2^p)
+  // The compositing backward accumulates q = (dL/dalpha) 2^p = dL/do per pair,
+  // with alpha = o 2^p, p = pa dx^2 + pb dx dy + pc dy^2, dx = px - u and the
+  // stored (pa, pb, pc) = -log2(e) (a/2, b, c/2) of the conic (a, b, c):
+  // G2[0..4] = sum q (dx, dy, dx^2, dx dy, dy^2). dL/dp = ln 2 o q, and pa, pb, pc
+  // are constant per Gaussian: with S = o G2, dL/du = -ln2 (2 pa S[0] + pb S[1])
+  // = a S[0] + b S[1] (likewise for v), dL/da = -ln2 log2(e) S[2] / 2 = -S[2] / 2
+  // and dL/db = -S[3].
+  const float op = a.opacities[k];
+  const float g_u = op * (A00 * G2[0] + A01 * G2[1]);
+  const float g_v = op * (A01 * G2[0] + A11 * G2[1]);
+  const float g_a = op * (-0.5f * G2[2]);
+  const float g_b = op * -G2[3];
+  const float g_c = op * (-0.5f * G2[4]);
+  go += G2[5];
   gc[0] += G2[6];
   gc[1] += G2[7];
   gc[2] += G2[8];
@@ -390,7 +392,6 @@ __global__ __launch_bounds__(256, 4) void k_project_bwd(Raster Rr, ProjectBwdArg
       __syncthreads();
     }
   }
-  if (go != 0.f) go /= a.opacities[k];  // the views' sums of q: dL/do = sum q / o (alpha = o 2^p)
   if (a.adam.on && a.adam.reg_w != 0.f && k < a.n) {
     float d[3];
     (void)reg_term(a.scales[3 * k], a.scales[3 * k + 1], a.scales[3 * k + 2], a.adam.reg_w, d);

@@ -25,8 +25,8 @@
 // transmittance in front of Gaussian j is recomputed as T_j = T_{j+1} /
 // (1 - alpha_j) instead of being stored; suffix sums of c alpha T and z alpha
 // T give the second terms of dC/dalpha and Eq. 8. Per pair, ten partials
-// (sums of q (dx, dy, dx^2, dx dy, dy^2, 1) with q = dL/dp / ln 2 for
-// alpha = o 2^p, then colour and direct depth; six of them for a pose-only
+// (sums of q (dx, dy, dx^2, dx dy, dy^2, 1) with q = dL/do = dL/dp / (o ln 2)
+// for alpha = o 2^p, then colour and direct depth; six of them for a pose-only
 // backward) are summed over the pixels of a wave's 8x8 block, four records at
 // a time, on the matrix cores (see bwd_item), and a record's sums go out with
 // one atomic per field. Each wave fetches, tests and walks its records by
@@ -446,7 +446,7 @@ __device__ __forceinline__ BwdPix bwd_pixel(const Raster& Rr, const BwdArgs& a, 
 //
 // The sums over the block's pixels are contractions and run on the matrix
 // cores, in FP32 (4x4x1 outer products, exact fused multiply-adds). With q =
-// dL/dp / ln 2 and wt = alpha T of the step's four records:
+// dL/do and wt = alpha T of the step's four records:
 //  - g . c (upstream gradient dot colour and depth) of four records: four
 //    outer products of the records' channels with the pixels' gradients;
 //  - q and wt are transposed inside each group of four lanes, so that a lane
@@ -462,8 +462,7 @@ __device__ __forceinline__ BwdPix bwd_pixel(const Raster& Rr, const BwdArgs& a, 
 //    pixels' gradients.
 // The 16 groups are then added by exchanges that split the fields over the
 // lanes, and one 40-lane atomic adds the four records' fields to the [n, 10]
-// gradient sums. The sum over q alone is o dL/do (the projection backward
-// divides by the opacity).
+// gradient sums (the projection backward multiplies the moments by the opacity).
 //
 // Bound by VALU issue (about 0.9 while a CU is busy): some 200 issue slots per
 // step of four records, where DPP sums of every pair's ten products and one
@@ -592,8 +591,7 @@ __device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, con
         b.gS = fmaf(gc[s], wt, b.gS);
         b.T = Tj;
         // a clamped alpha does not depend on o or sigma
-        const float gp = (hit & !pe.clamped) ? dA * pe.alpha : 0.f;
-        qT[s] = gp;
+        qT[s] = (hit & !pe.clamped) ? dA * pe.e : 0.f;
         wT[s] = wt;
       }
       transpose4(qT, wT, 0x5555555555555555ull, 0x3333333333333333ull);

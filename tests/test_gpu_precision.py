@@ -101,3 +101,19 @@ def test_opacities_below_an_alpha_gradient():
     err = np.concatenate(errs)
     print(f"dL/do: rms {rms(err):.2e}, largest {np.abs(err).max():.2e}")
     assert rms(err) <= 2 * 2.0 ** -24
+
+
+def test_opacity_gradient_is_the_sum_itself():
+    """One Gaussian that fills the image at alpha = o = 3/4, an upstream gradient
+    of alpha alone: T, its reciprocal and the per-pixel gradients are exact, 256
+    equal ones add up exactly, and so dL/do = 256 ga, with no rounding at all."""
+    import torch
+    W = 16
+    g = dev([[0, 0, 1]], np.full((1, 3), 1e6), [[1.0, 0, 0, 0]], [0.75], np.zeros((1, 3)))
+    cam = gsr.make_camera(W, W, 64.0, 64.0, 8.0, 8.0, 0.2)
+    _, _, _, st = gsr.render_fwd(*g, eye(), cam)
+    zero = torch.zeros((W, W), device="cuda")
+    for ga in np.random.default_rng(0).uniform(1, 2, 64).astype(np.float32):
+        out = gsr.render_bwd(st, torch.zeros((3, W, W), device="cuda"), zero, torch.full((W, W), float(ga), device="cuda"))
+        assert float(out["opacities"][0]) == 256 * float(ga)
+    st.release()
