@@ -437,6 +437,25 @@ __device__ __forceinline__ BwdPix bwd_pixel(const Raster& Rr, const BwdArgs& a, 
   return b;
 }
 
+// The sums of wt (g_r, g_g, g_b, g_d) over a group's four pixels, for a block
+// with an upstream gradient that is not finite: a pixel that did not composite
+// the record (wt = 0) adds nothing to it, where an outer product would add 0
+// times that gradient, a NaN.
+template <int CTRL>
+__device__ __forceinline__ void add_if_hit(const BwdPix& b, float wt, f32x4& r) {
+  const f32x4 g = {dpp_all<CTRL>(b.g0), dpp_all<CTRL>(b.g1), dpp_all<CTRL>(b.g2), dpp_all<CTRL>(b.gd)};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = wt != 0.f ? fmaf(g[i], wt, r[i]) : r[i];
+}
+__device__ __forceinline__ f32x4 sums_of_hits(const BwdPix& b, const float (&wT)[4]) {
+  f32x4 r = {0.f, 0.f, 0.f, 0.f};
+  add_if_hit<0x00>(b, wT[0], r);
+  add_if_hit<0x55>(b, wT[1], r);
+  add_if_hit<0xaa>(b, wT[2], r);
+  add_if_hit<0xff>(b, wT[3], r);
+  return r;
+}
+
 // Backward of one wave's 8x8 block (block w of the item's tile), with NF = 10
 // fields (mapping) or 6 (a pose-only backward). The wave reads the records of
 // the tile's list in chunks of 64 from the largest `last` of its pixels
@@ -503,6 +522,8 @@ __device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, con
   const int b54 = ((lane >> 5) & 1) + 2 * ((lane >> 4) & 1);
   const int fld0 = NF == 10 ? (b2 ? 8 + b54 : 4 * (int)b3 + b54) : 4 * (int)b3 + b54;
   const int fld = NF == 10 ? ((b2 && (b3 || b54 > 1)) ? -1 : fld0) : ((b2 || fld0 > 5) ? -1 : fld0);
+  // some upstream gradient of the block is not finite (0 times it is NaN)
+  const bool odd = __ballot(!(0.f * b.g0 + 0.f * b.g1 + 0.f * b.g2 + 0.f * b.gd == 0.f)) != 0;
   float xs[4], G[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) xs[s] = (float)(q.blk.x0 + 4 * (q.quad & 1) + s);
@@ -597,6 +618,7 @@ __device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, con
       transpose4(qT, wT, 0x5555555555555555ull, 0x3333333333333333ull);
 #pragma unroll
       for (int s = 0; s < 4; ++s) Wm = outer4(G[s], wT[s], Wm);
+      if (odd) Wm = sums_of_hits(b, wT);
       // moments about the record's centre (u, v)
       float dx[4], qx[4];
 #pragma unroll

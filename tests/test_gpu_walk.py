@@ -160,3 +160,40 @@ def test_sort_networks_and_runs(lengths):
     K, ranges, ids = gsr.tile_lists(st, 9)
     assert K == sum(lengths)
     G.compare_tile_lists(ranges.cpu().numpy(), ids.cpu().numpy(), tl, None)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("which", ["color", "depth"])
+@pytest.mark.parametrize("n", [8, 40000])
+def test_non_finite_upstream_reaches_what_its_pixel_composited(bad, which, n):
+    """A non-finite upstream gradient at pixel (2, 2), of colour or of depth. The
+    gradients of records that pixel (2, 2) did not composite are what they are
+    without it, all of them: of records in the same steps of the walk around
+    another pixel of the block, of one (the seventh) that passes the block's test
+    between two pixels and meets none, and of records of another block; in double
+    and in float sums (every record lies in one block, so that those have no order)."""
+    px = np.array([2, 5, 2, 5, 13, 5, 8.8, 13], np.float64)
+    py = np.array([2, 5, 2, 5, 3, 5, 3.5, 3], np.float64)
+    z = np.concatenate([1.0 + 0.05 * np.arange(8), np.full(n - 8, -1.0)])
+    m = np.zeros((n, 3))
+    m[:8, 0], m[:8, 1] = (px - CAM.cx) / CAM.fx * z[:8], (py - CAM.cy) / CAM.fy * z[:8]
+    m[:, 2] = z
+    g = G.f32(dict(means=m, scales=np.full((n, 3), 0.02), quats=np.tile([1.0, 0, 0, 0], (n, 1)),
+                   opacities=np.full(n, 0.3), colors=np.full((n, 3), 0.5)))
+    bare = {k: np.delete(v, [0, 2], 0) for k, v in g.items()}  # without the records of the pixel
+    gC = np.full((3, CAM.height, CAM.width), 0.5, np.float32)
+    gD = np.full((CAM.height, CAM.width), 0.25, np.float32)
+    want, pose = backward(g, gC, gD, want_pose=False), backward(bare, gC, gD)
+    (gC[1] if which == "color" else gD)[2, 2] = bad
+    got = backward(g, gC, gD, want_pose=False)
+    reached = np.zeros(n, bool)
+    reached[[0, 2]] = True
+    for k in gsr.PARAM_GROUPS:
+        np.testing.assert_array_equal(got[k][~reached], want[k][~reached], err_msg=k)
+    for k in ("means", "opacities"):
+        assert not np.isfinite(got[k][reached]).any(), k
+    # ten sums and the pose's six, where the pixel composited nothing
+    for kw in (dict(), dict(want_params=False)):
+        out = backward(bare, gC, gD, **kw)
+        for k in ("pose7", "twist6"):
+            np.testing.assert_allclose(out[k], pose[k], rtol=1e-5, atol=1e-6 * np.abs(pose[k]).max())
