@@ -184,7 +184,8 @@ int gsr_render_bwd_adam(gsr_ctx *ctx, gsr_state *state, const float *dL_dcolor, 
  * gradients, writes the fastest shape into opts->tile_w / tile_h (the other
  * fields are inputs) and the fastest blocks_per_cu into *best_blocks_per_cu.
  * The backward timed is the mapping one (gradients of all five parameter
- * groups). ms_table (may be NULL) receives the 15 mean times, shape-major.
+ * groups). ms_table (may be NULL) receives the 15 mean times, shape-major;
+ * 8 gives the launches of 0 and has its time, so *best_blocks_per_cu is not 8.
  * Allocates scratch images and gradients; synchronises. */
 int gsr_autotune_batch(gsr_ctx *ctx, const gsr_gaussians *g, int32_t n_views, const gsr_camera *cam, gsr_opts *opts,
                        const float *poses7, const float *dL_dcolor, const float *dL_ddepth, int32_t reps,

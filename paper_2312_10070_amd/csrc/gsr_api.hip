@@ -1205,12 +1205,16 @@ int gsr_autotune_batch(gsr_ctx* c, const gsr_gaussians* g, int32_t n_views, cons
   }
   const int shapes[3][2] = {{16, 16}, {8, 32}, {32, 8}};
   const int bpc[5] = {0, 1, 2, 4, 8};
-  float best = 1e30f;
+  float best = 1e30f, plain = 0.f;  // of the shape, with one workgroup per item
   int best_s = 0, best_b = 0, rc = GSR_OK;
   const bool prof = c->prof;
   c->prof = false;
   for (int si = 0; si < 3 && rc == GSR_OK; ++si)
     for (int bi = 0; bi < 5 && rc == GSR_OK; ++bi) {
+      if (bpc[bi] >= std::max(gsr::kFwdHeld, gsr::kBwdHeld)) {  // the same launches as with 0
+        if (ms_table) ms_table[si * 5 + bi] = plain;
+        continue;
+      }
       gsr_opts o = *opts;
       o.tile_w = shapes[si][0];
       o.tile_h = shapes[si][1];
@@ -1229,6 +1233,7 @@ int gsr_autotune_batch(gsr_ctx* c, const gsr_gaussians* g, int32_t n_views, cons
         }
       }
       const float avg = total / reps;
+      if (bpc[bi] == 0) plain = avg;
       if (ms_table) ms_table[si * 5 + bi] = avg;
       if (rc == GSR_OK && avg < best) {
         best = avg;

@@ -108,6 +108,20 @@ def test_autotune_picks_a_timed_configuration():
     assert table[(best.tile_w, best.tile_h, bpc)] == min(table.values())
 
 
+def test_autotune_times_a_launch_once():
+    """8 workgroups per unit asked for are more than a unit holds: one workgroup
+    per item is launched, as with 0. The two share a time, and 8 is not chosen."""
+    torch = torch_()
+    inp, g, poses = batch_scene(1, n=30_000, V=3)
+    args = (g["means"], g["scales"], g["quats"], g["opacities"], g["colors"])
+    gC = torch.full((3, 3, CAM.height, CAM.width), 1e-3, device="cuda")
+    gD = torch.full((3, CAM.height, CAM.width), 1e-3, device="cuda")
+    best, bpc, table = gsr.autotune_batch(*args, poses, gsr.camera_from(CAM), gC, gD, reps=2)
+    for shape in ((16, 16), (8, 32), (32, 8)):
+        assert table[(*shape, 8)] == table[(*shape, 0)] > 0
+    assert bpc in (0, 1, 2, 4)
+
+
 def test_persistent_grid_takes_the_longest_list_first():
     """500 lists on a persistent grid of 256 workgroups, one of them twice as
     long as the others, in the first tile or in the last. Taken first in both,
