@@ -272,11 +272,25 @@ __device__ __forceinline__ Item item_at(const ItemOrder& o, const int2* __restri
   }
   return r;
 }
+// Compute units of the chip. (A partition of it has fewer: what follows from
+// this number there is no longer the best split or order, but a right one.)
+constexpr int kUnits = 256;
+// Workgroups of the compositing passes that a compute unit holds (forward: 26
+// of its 160 KB of LDS each; backward: 20 waves of at most 96 registers). A
+// persistent grid of as many or more per compute unit bounds nothing, and one
+// workgroup per item is faster, as no workgroup waits for its slowest wave
+// between items: 8 views of 1200x680, 1M Gaussians, 474 -> 358 us forward
+// and 986 -> 880 us backward. A smaller grid is run as asked for.
+constexpr int kFwdHeld = 6, kBwdHeld = 5;
+
 // Workgroups per view: 1,024 Gaussians each, at most 128, and over all views at
-// most about one per compute unit. Every workgroup reserves room on every tile
-// it meets, with an atomic on a word that all of the view's workgroups share:
-// 8 views of 1M, 128 per view 120 us counting and 98 placing, 64 109 and 98, 32
-// 98 and 92; one view, 256 instead of 128 24 us instead of 20 and 21 each.
+// most one per compute unit, but four per view. Every workgroup reserves room
+// on every tile it meets, with an atomic on a word that all of the view's
+// workgroups share: 8 views of 1M, 128 per view 120 us counting and 98 placing,
+// 64 109 and 98, 32 98 and 92; one view, 256 instead of 128 24 us instead of 20
+// and 21 each. 17 views of 640x480 of 200K, counting and placing with the sort,
+// 15 per view 66 and 110 us, 16 (one in the last round) 72 and 122; 64 views,
+// four 253 and 412, eight 262 and 411, 16 272 and 409, 32 276 and 375.
 int bin_workgroups(int64_t n, int64_t views);
 // M, R and K from the tile rectangles (LDS histograms, one reservation atomic
 // per (tile, workgroup), the last workgroup scans the tile totals).
@@ -302,14 +316,6 @@ struct FwdArgs {
   int blocks;                 // persistent launch: workgroups (0 = one per item)
 };
 void launch_render_fwd(const Raster& R, const FwdArgs& a, hipStream_t s);
-
-// Workgroups of the compositing passes that a compute unit holds (forward: 26
-// of its 160 KB of LDS each; backward: 20 waves of at most 96 registers). A
-// persistent grid of as many or more per compute unit bounds nothing, and one
-// workgroup per item is faster, as no workgroup waits for its slowest wave
-// between items: 8 views of 1200x680, 1M Gaussians, 474 -> 358 us forward
-// and 986 -> 880 us backward. A smaller grid is run as asked for.
-constexpr int kFwdHeld = 6, kBwdHeld = 5;
 
 // The compositing backward adds a Gaussian's sums with atomics, in an order
 // that varies from run to run. Up to this many (Gaussian, view) pairs the

@@ -161,16 +161,15 @@ __device__ __forceinline__ Chunk bin_chunk(const Raster& Rr, const BinArgs& a) {
 
 // Bucket of a list length, longest first: 16 buckets per power of two.
 constexpr int kOrderBuckets = 512;
-constexpr int kUnits = 256;  // compute units of the chip
-// Workgroups a compute unit holds of the backward. Up to as many rounds of
-// items are all dealt out at the start, in turn over the compute units, and
+// Up to as many rounds of items as a compute unit holds workgroups of the
+// backward are all dealt out at the start, in turn over the compute units, and
 // none moves later. Each full round then goes out shortest first, so that the
 // units that get no item of the last, partial round are those with the longest
 // of each round before: backward 640x480 (4.7 rounds) of 500K 120 -> 114 us, of
 // 300K 90 -> 84 us (the sums of the lists' lengths per unit come to 1.14 of
 // their mean instead of 1.24), forward 66 -> 68 and 41 -> 40. With 6.8 rounds
 // (801x533) nothing changes.
-constexpr int kHeldRounds = 5;
+constexpr int kHeldRounds = kBwdHeld;
 static_assert((kUnits & (kUnits - 1)) == 0, "a round is reversed by flipping its index bits");
 __device__ __forceinline__ int order_bucket(uint32_t len) {
   const int b = (int)(__float_as_uint((float)len) >> 19) - (127 << 4);
@@ -642,7 +641,7 @@ void launch_exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_
 
 int bin_workgroups(int64_t n, int64_t views) {
   const int64_t w = (n + 1023) / 1024;
-  const int64_t most = std::max<int64_t>(16, std::min<int64_t>(128, kUnits / std::max<int64_t>(views, 1)));
+  const int64_t most = std::max<int64_t>(4, std::min<int64_t>(128, kUnits / std::max<int64_t>(views, 1)));
   return (int)(w < 1 ? 1 : (w > most ? most : w));
 }
 
@@ -670,9 +669,10 @@ void launch_tile_bins(const Raster& R, const BinArgs& a, int64_t n_items, int2* 
   hipLaunchKernelGGL(k_bin_place, bin_grid(R, b), dim3(kPlaceThreads), bin_lds(R), s, R, b);
   // Few items: a workgroup for each, so that all four waves share a long one
   // (1,200 lists, all of 1100 keys 73 -> 40 us with placement, of 300 the same);
-  // beyond what the chip holds at a time, one for each wave (3,225 lists of 300
-  // 37 -> 32 us, 25,800 187 -> 160).
-  const int per = n_items <= kHeldRounds * kUnits ? 1 : kBinThreads / 64;
+  // from some rounds of workgroups on, one for each wave (3,225 lists of 300 37
+  // -> 32 us, 25,800 187 -> 160).
+  constexpr int64_t kOneEach = 5 * kUnits;
+  const int per = n_items <= kOneEach ? 1 : kBinThreads / 64;
   hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)((n_items + per - 1) / per)),
                      dim3(kBinThreads), 0, s, (const int2*)ranges, (int)n_items, per, a.keys, scratch, ids, order);
 }
