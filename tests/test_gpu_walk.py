@@ -197,3 +197,54 @@ def test_non_finite_upstream_reaches_what_its_pixel_composited(bad, which, n):
         out = backward(bare, gC, gD, **kw)
         for k in ("pose7", "twist6"):
             np.testing.assert_allclose(out[k], pose[k], rtol=1e-5, atol=1e-6 * np.abs(pose[k]).max())
+
+
+@pytest.mark.parametrize("ntx,nty", [(27, 19), (40, 30), (40, 32), (61, 21), (128, 64), (211, 39)])
+def test_tiles_by_length_equal_tiles_in_place(ntx, nty):
+    """513, 1,200, 1,280, 1,281, 8,192 and 8,229 tiles with K >= 2^18, which are
+    taken by length: two rounds of 256 reversed and one tile more, a partial last
+    round, five full rounds, one tile more than rounds are reversed for, one
+    stretch of the ordering, and a ragged second. Images and gradients (the
+    deterministic option) against those of windows of at most 512 tiles, which
+    are taken as they lie, equal to the bit: every Gaussian lies in one tile, all
+    coordinates are exact in both frames. (The scenes above have fewer entries,
+    and their tiles are taken as they lie.)"""
+    import torch
+    f, n_tiles = 4096.0, ntx * nty
+    rng = np.random.default_rng(n_tiles)
+    lengths = rng.integers(0, 2 * (1 << 18) // n_tiles + 40, n_tiles)
+    lengths[rng.integers(0, n_tiles, 20)] += 700
+    t = rng.permutation(np.repeat(np.arange(n_tiles), lengths))
+    n = len(t)
+    u = 16 * (t % ntx) + 7.5 + rng.integers(-128, 129, n) / 64
+    v = 16 * (t // ntx) + 7.5 + rng.integers(-128, 129, n) / 64
+    cx, cy = 8.0 * ntx, 8.0 * nty
+    d = G.to_dev(dict(means=np.stack([(u - cx) / f, (v - cy) / f, np.ones(n)], 1),
+                      scales=rng.uniform(0.2, 0.8, (n, 3)) / f, quats=rng.normal(size=(n, 4)),
+                      opacities=rng.uniform(0.02, 0.4, n), colors=rng.uniform(0, 1, (n, 3))))
+    pose = torch.tensor(POSE.astype(np.float32), device="cuda")
+    gC = torch.from_numpy(rng.normal(size=(3, 16 * nty, 16 * ntx)).astype(np.float32)).cuda()
+    gD = torch.from_numpy(rng.normal(size=(16 * nty, 16 * ntx)).astype(np.float32)).cuda()
+
+    def run(x0, x1, y0, y1):
+        camera = gsr.make_camera(16 * (x1 - x0), 16 * (y1 - y0), f, f, cx - 16 * x0, cy - 16 * y0, 0.2)
+        sl = (slice(16 * y0, 16 * y1), slice(16 * x0, 16 * x1))
+        *img, st = gsr.render_fwd(d["means"], d["scales"], d["quats"], d["opacities"], d["colors"], pose, camera,
+                                  gsr.RasterOpts(deterministic=1))
+        K = gsr.tile_lists(st, (x1 - x0) * (y1 - y0))[0]
+        out = gsr.render_bwd(st, gC[(slice(None), *sl)].contiguous(), gD[sl].contiguous(), want_pose=False)
+        st.release()
+        return img, out, K, sl
+
+    (color, depth, alpha), grads, K, _ = run(0, ntx, 0, nty)
+    assert K == n >= 1 << 18 and n_tiles > 512
+    parts = {k: torch.zeros_like(x) for k, x in grads.items()}
+    for y0 in range(0, nty, 16):
+        for x0 in range(0, ntx, 32):
+            img, out, _, sl = run(x0, min(x0 + 32, ntx), y0, min(y0 + 16, nty))
+            assert torch.equal(color[(slice(None), *sl)], img[0])
+            assert torch.equal(depth[sl], img[1]) and torch.equal(alpha[sl], img[2])
+            for k in gsr.PARAM_GROUPS:
+                parts[k] += out[k]
+    for k in gsr.PARAM_GROUPS:
+        assert torch.equal(grads[k], parts[k]) and bool((grads[k] != 0).any()), k
