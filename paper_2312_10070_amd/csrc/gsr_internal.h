@@ -258,19 +258,11 @@ struct ItemOrder {
   const uint32_t* K;  // by length if *K >= least
   uint32_t least;
 };
-// The item that is taken i-th, where item `at` stands in for it, and its
-// range. K, the order and the range that it may be are read side by side.
-struct Item {
-  int index;
-  int2 range;
-};
-__device__ __forceinline__ Item item_at(const ItemOrder& o, const int2* __restrict__ ranges, int i, int at) {
-  Item r{at, ranges[at]};
-  if (o.items) {
-    const int it = o.items[i];
-    if (*o.K >= o.least) r = Item{it, ranges[it]};
-  }
-  return r;
+// The item that is taken i-th, where item `at` stands in for it.
+__device__ __forceinline__ int item_at(const ItemOrder& o, int i, int at) {
+  if (!o.items) return at;
+  const int it = o.items[i];  // (read beside K, not after it)
+  return *o.K >= o.least ? it : at;
 }
 // Compute units of the chip. (A partition of it has fewer: what follows from
 // this number there is no longer the best split or order, but a right one.)

@@ -203,11 +203,12 @@ __device__ __forceinline__ void init_smem(FwdSmem& sm) {
 // before the pixel stops, and pairs composited. The lists then come from the
 // support boxes alone, so every such pair is visited.
 template <bool STATS>
-__device__ __forceinline__ void fwd_item(const Raster& Rr, const FwdArgs& a, const Item& item, FwdSmem& sm) {
+__device__ __forceinline__ void fwd_item(const Raster& Rr, const FwdArgs& a, int item, FwdSmem& sm) {
   constexpr int kBatch = FwdSmem::kBatch, kDummy = FwdSmem::kDummy;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const Pixel q = item_pixel(Rr, item.index);
-  const int start = item.range.x, end = item.range.y;
+  const Pixel q = item_pixel(Rr, item);
+  const int2 rg = a.ranges[item];
+  const int start = rg.x, end = rg.y;
   // T > 0: the lane is compositing; T < 0: it has stopped and -T is its final
   // transmittance (T >= T_min > 0 while compositing, so the sign is free).
   float T = q.inside ? 1.f : -1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, D = 0.f;
@@ -509,10 +510,10 @@ __device__ __forceinline__ f32x4 sums_of_hits(const BwdPix& b, const float (&wT)
 // gradient a thousand times the colour's, 200 layers: dL/do off by 2.1e-7 rms,
 // so 6.0e-8). A kernel of its own, as the operation costs the others 3 %.
 template <int NF, BwdSums SUMS, bool ALPHA>
-__device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, const Item& item, BwdWave* smem) {
+__device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, int item, BwdWave* smem) {
   constexpr int H = NF / 2;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const Pixel q = item_pixel(Rr, item.index);
+  const Pixel q = item_pixel(Rr, item);
   BwdPix b = bwd_pixel(Rr, a, q);
   // per-lane constants: lane 4 b + i holds, for pixel s of block b, row i of
   // the upstream gradients, and the pixel's x
@@ -537,7 +538,7 @@ __device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, con
   GSR_GRAD_ROW(2, 0xaa)
   GSR_GRAD_ROW(3, 0xff)
 #undef GSR_GRAD_ROW
-  const int start = item.range.x;
+  const int start = a.ranges[item].x;
   const int wmax = __builtin_amdgcn_readfirstlane(wave_max_int(b.last));
   BwdWave& sm = smem[w];
 
@@ -681,43 +682,47 @@ __global__ __launch_bounds__(kTileThreads) void k_render_fwd(Raster Rr, FwdArgs 
   __shared__ FwdSmem sm;
   init_smem(sm);
   const int b = (int)blockIdx.x;
-  fwd_item<STATS>(Rr, a, item_at(a.order, a.ranges, b, xcd_tile(b, (int)gridDim.x)), sm);
+  fwd_item<STATS>(Rr, a, item_at(a.order, b, xcd_tile(b, (int)gridDim.x)), sm);
 }
 
 template <int NF, BwdSums SUMS, bool ALPHA>
 __global__ __launch_bounds__(kTileThreads, 5) void k_render_bwd(Raster Rr, BwdArgs a) {
   __shared__ BwdWave sm[kWavesPerTile];
   const int b = (int)blockIdx.x;
-  bwd_item<NF, SUMS, ALPHA>(Rr, a, item_at(a.order, a.ranges, b, xcd_chunk(b, (int)gridDim.x)), sm);
+  bwd_item<NF, SUMS, ALPHA>(Rr, a, item_at(a.order, b, xcd_chunk(b, (int)gridDim.x)), sm);
 }
 
 // Persistent workgroups: take the next item from the queue until it is empty.
 // Every workgroup reaches the exit once the counter passes n_items.
-template <class Args>
-__device__ __forceinline__ bool next_item(const Args& a, int* s_item, Item& item) {
+__device__ __forceinline__ int next_item(int* queue, const ItemOrder& order, int n_items, int* s_item) {
   __syncthreads();
-  if (threadIdx.x == 0) *s_item = atomicAdd(a.queue, 1);
+  if (threadIdx.x == 0) *s_item = atomicAdd(queue, 1);
   __syncthreads();
   const int qi = *s_item;
-  if (qi >= a.n_items) return false;
-  item = item_at(a.order, a.ranges, qi, qi);
-  return true;
+  if (qi >= n_items) return -1;
+  return item_at(order, qi, qi);
 }
 
 __global__ __launch_bounds__(kTileThreads) void k_render_fwd_persistent(Raster Rr, FwdArgs a) {
   __shared__ FwdSmem sm;
   __shared__ int s_item;
   init_smem(sm);
-  Item item;
-  while (next_item(a, &s_item, item)) fwd_item<false>(Rr, a, item, sm);
+  for (;;) {
+    const int item = next_item(a.queue, a.order, a.n_items, &s_item);
+    if (item < 0) break;
+    fwd_item<false>(Rr, a, item, sm);
+  }
 }
 
 template <int NF, BwdSums SUMS>
 __global__ __launch_bounds__(kTileThreads, 5) void k_render_bwd_persistent(Raster Rr, BwdArgs a) {
   __shared__ BwdWave sm[kWavesPerTile];
   __shared__ int s_item;
-  Item item;
-  while (next_item(a, &s_item, item)) bwd_item<NF, SUMS, true>(Rr, a, item, sm);
+  for (;;) {
+    const int item = next_item(a.queue, a.order, a.n_items, &s_item);
+    if (item < 0) break;
+    bwd_item<NF, SUMS, true>(Rr, a, item, sm);
+  }
 }
 
 // Deterministic backward, before the compositing pass: rev[goff[o] + j] =

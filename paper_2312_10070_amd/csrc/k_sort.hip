@@ -561,8 +561,8 @@ __global__ __launch_bounds__(kBinThreads) void k_tile_sort(const int2* __restric
     const int it = threadIdx.x & 3;
     const int i = (int)blockIdx.x + it * (int)gridDim.x, p = (int)blockIdx.x * per + it;
     const bool by_length = ord.items && *ord.K >= ord.least;
-    rg = item_at(ord, ranges, min(i, n_items - 1), min(p, n_items - 1)).range;
-    if (it >= per || (by_length ? i : p) >= n_items) rg = make_int2(0, 0);
+    const int item = item_at(ord, min(i, n_items - 1), min(p, n_items - 1));
+    rg = it < per && (by_length ? i : p) < n_items ? ranges[item] : make_int2(0, 0);
   }
   auto pick = [&](int it) {
     return make_int2(__builtin_amdgcn_readlane(rg.x, it), __builtin_amdgcn_readlane(rg.y, it));
