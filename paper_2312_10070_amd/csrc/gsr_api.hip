@@ -479,7 +479,8 @@ gsr::BinArgs bin_args(const gsr_ctx* c, gsr_state* s, int64_t cap, uint32_t* K_h
 // workgroups or (0) one per item.
 gsr::ItemOrder item_order(const gsr_state* s, int blocks) {
   if (blocks > 0) return {s->order, s->d_K, 0};
-  return {s->R.n_tiles * s->n_views > gsr::kOrderItems ? s->order : nullptr, s->d_K, gsr::kOrderEntries};
+  const int n = s->R.n_tiles * s->n_views;
+  return {n > gsr::kOrderItems ? s->order : nullptr, s->d_K, gsr::order_least(n)};
 }
 
 // Projection, per-(tile, workgroup) pair counts, the tiles' ranges and the

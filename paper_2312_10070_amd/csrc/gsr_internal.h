@@ -245,7 +245,13 @@ struct BinArgs {
 // and backward, 320x240 with 31K Gaussians (K about 65,000) 41.8 -> 45.9 us and
 // 84.2 -> 85.7, 560x360 with 81K (170,000) 53.4 -> 55.1 and 112 -> 111, with
 // 242K (390,000) 93.2 -> 92.0 and 207 -> 195, 800x500 with 480K 138 -> 121 and
-// 329 -> 301. n is asked where the launch is made, K on the device, where it
+// 329 -> 301. Nor where there are many items and most have a short list, as one
+// workgroup makes the order; binning to backward, even scenes and ones with half
+// of the entries in a sixteenth of the image: 262,144 items with 2 entries each
+// 2551 -> 2911 us and 2437 -> 2744, with 22 3530 -> 3976 and 3901 -> 4010;
+// 65,536 with 9 722 -> 794 and 776 -> 781, with 29 953 -> 1043 and 1169 -> 1029,
+// with 88 1640 -> 1723 and 2296 -> 1721; 14,400 with 40 243 -> 251 and 314 ->
+// 262. n is asked where the launch is made, K on the device, where it
 // is known: what a state's workspace has room for says nothing about this call.
 // A persistent grid's workgroups take the longest first whatever n and K are: a
 // long list that one of them takes last is what the launch ends with (forward,
@@ -253,6 +259,10 @@ struct BinArgs {
 // by position, 185 by length).
 constexpr int kOrderItems = 512;
 constexpr uint32_t kOrderEntries = 1 << 18;
+__host__ __device__ __forceinline__ uint32_t order_least(int64_t n) {  // K from which on n items go by length
+  const int64_t k = 24 * n > kOrderEntries ? 24 * n : kOrderEntries;
+  return k < 0xffffffffll ? (uint32_t)k : 0xffffffffu;
+}
 struct ItemOrder {
   const int* items;   // NULL = by position
   const uint32_t* K;  // by length if *K >= least

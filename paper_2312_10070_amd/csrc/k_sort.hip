@@ -230,7 +230,7 @@ __device__ uint32_t scan_tile_totals(uint32_t* T, int2* R, int* order, uint32_t*
     }
     carry += tot;
   }
-  if (!kAlways && (n <= kOrderItems || carry < kOrderEntries)) return carry;  // no launch goes by the order
+  if (!kAlways && (n <= kOrderItems || carry < order_least(n))) return carry;  // no launch goes by the order
   constexpr int64_t kStretch = (int64_t)kPlaceThreads * kScanItems;
   for (int64_t b0 = (n - 1) / kStretch * kStretch; b0 >= 0; b0 -= kStretch) {
     const int64_t base = b0 + (int64_t)threadIdx.x * kScanItems;

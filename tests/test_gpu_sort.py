@@ -87,3 +87,28 @@ def test_a_call_costs_the_same_whatever_its_context_served_before():
     ctx.lib.gsr_ctx_destroy(ctypes.c_void_p(ctx.h.value) if hasattr(ctx.h, "value") else ctx.h)
     print(f"tile lists: {1e3 * fresh:.1f} us in a fresh context, {1e3 * after:.1f} us after a larger call")
     assert after < 1.2 * fresh
+
+
+def test_many_short_lists_are_not_ordered():
+    """65,536 tiles of four entries, just below and just above the 2^18 entries
+    from which on the passes may go by length: the counting pass does not begin
+    to make an order there (a third of its time), which would gain nothing."""
+    import torch
+
+    def stage(entries):
+        lengths = np.full(256 * 256, 4)
+        lengths[:abs(entries)] += np.sign(entries)
+        g, pose, cam, _, _ = frame(256, 256, lengths)
+        got = []
+        for _ in range(15):
+            gsr.profile_enable(True)
+            gsr.render_fwd(*g, pose, cam)[3].release()
+            torch.cuda.synchronize()
+            gsr.profile_enable(False)
+            ms, calls = gsr.profile_read()["bin_count"]
+            got.append(ms / calls)
+        return min(got)
+
+    below, above = stage(-2000), stage(2000)
+    print(f"counting: {1e3 * below:.1f} us below 2^18 entries, {1e3 * above:.1f} us above")
+    assert above < 1.15 * below
