@@ -22,6 +22,9 @@
 // of the means, or two where they straddle blocks. The squared distance
 // (dx^2 + dy^2) + dz^2 is evaluated without contraction, and the minimum is
 // exact, so results do not depend on the order in which the grid is filled.
+#include <algorithm>
+#include <cfloat>
+
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -297,7 +300,9 @@ static int64_t seed_pts_offset(int64_t T, int64_t n) { return (seed_rank_offset(
 
 int64_t seed_temp_words(int64_t n) { return seed_pts_offset(seed_buckets(n), n) + 4 * n; }
 
-// the cell edge h = r_max (1 + 1e-3) as its reciprocal
+// the cell edge h = r_max (1 + 1e-3), and its reciprocal; for the largest r_max
+// the largest float, as 0 times an infinite edge would be no bound
+static float seed_h(float r_max) { return (float)std::min((double)r_max * 1.001, (double)FLT_MAX); }
 static float seed_inv_h(float r_max) { return (float)(1.0 / ((double)r_max * 1.001)); }
 
 void launch_seed_grid(const float* means, int64_t n, float r_max, uint32_t* temp, hipStream_t s) {
@@ -329,7 +334,7 @@ void launch_seed_query(int64_t n, const float* points, int64_t m, float rho, flo
     const int64_t mj = m - j < kSlice ? m - j : kSlice;
     const unsigned gm = (unsigned)((mj * kLanes + 255) / 256);
     hipLaunchKernelGGL(k_seed_query, dim3(gm), dim3(256), 0, s, points + 3 * j, mj, seed_inv_h(r_max),
-                       (float)((double)r_max * 1.001), T / kRow - 1, offsets, pts, r2max, rho2,
+                       seed_h(r_max), T / kRow - 1, offsets, pts, r2max, rho2,
                        nn_d2 ? nn_d2 + j : nullptr, keep ? keep + j : nullptr);
   }
 }

@@ -114,6 +114,22 @@ def test_seed_query_rows_and_blocks(base, per):
     np.testing.assert_array_equal(keep, np.where(nn < np.float32(rho) * np.float32(rho), 0, 1))
 
 
+@pytest.mark.parametrize("r_max", [float(np.finfo(np.float32).max), 3.4e38, 1e30, 1e19])
+def test_seed_query_without_a_bound(r_max):
+    """r_max as large as a float goes (its square is infinite, and for the first
+    two the cell edge beyond it too): the distance to the nearest mean, also
+    where that lies on the other side of a coordinate plane, in another cell."""
+    rng = np.random.default_rng(3)
+    p = rng.uniform(-2, 0, (40, 3)).astype(np.float32)
+    q = rng.uniform(-2, 2, (500, 3)).astype(np.float32)
+    q[:8] = 0.0
+    d = q[:, None, :] - p[None]
+    want = ((d[..., 0] * d[..., 0] + d[..., 1] * d[..., 1]) + d[..., 2] * d[..., 2]).min(1)
+    nn, keep = run(p, q, 0.25, r_max)
+    np.testing.assert_array_equal(nn, want)
+    np.testing.assert_array_equal(keep, np.where(want < np.float32(0.0625), 0, 1))
+
+
 def test_seed_query_bad_arguments():
     torch = torch_()
     p = dev(np.zeros((4, 3)))
