@@ -366,7 +366,8 @@ class Scratch {
     }
     if (s_->bytes < bytes) {
       release_dev();
-      const size_t room = std::max(bytes + bytes / 4, size_t(1) << 20);
+      // (what will not be kept needs no room for a larger call)
+      const size_t room = bytes > kKeep ? bytes : std::min(std::max(bytes + bytes / 4, size_t(1) << 20), kKeep);
       if (hipMalloc(&s_->dev, room) == hipSuccess) {
         s_->bytes = room;
       } else {

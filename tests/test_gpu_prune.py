@@ -150,3 +150,21 @@ def test_kept_scratch_serves_other_sizes_threads_and_streams():
     for t in threads:
         t.join()
     assert not failures, failures[0]
+
+
+@pytest.mark.parametrize("n,kept", [(6_000_000, True), (8_000_000, False)])
+def test_scratch_is_kept_up_to_its_bound(n, kept):
+    """Neighbour queries against 6M means take 243 MiB of temporary memory, within
+    the 256 MiB that a context keeps, against 8M 281 MiB, which it gives back."""
+    import ctypes
+    torch = torch_()
+    p = torch.rand((n, 3), device="cuda")
+    q = torch.rand((8, 3), device="cuda")
+    ctx = gsr.Context(0)
+    gsr.seed_query(p, q, 0.001, 0.002)  # (code and outputs are in place)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    gsr.seed_query(p, q, 0.001, 0.002, ctx=ctx)
+    held = (free - torch.cuda.mem_get_info()[0]) / 2 ** 20
+    ctx.lib.gsr_ctx_destroy(ctypes.c_void_p(ctx.h.value))
+    assert (240 < held < 262) if kept else held < 8, held
