@@ -58,14 +58,12 @@ def stage_work(stage: str, st: dict, n: int, P: int) -> tuple[str, float]:
         return "alu", FLOPS_EVAL * st["pairs_fwd"] + FLOPS_COMP_FWD * st["pairs_composited"]
     if stage == "render_bwd":
         return "alu", FLOPS_EVAL * st["pairs_bwd"] + FLOPS_COMP_BWD * st["pairs_composited"]
-    if stage == "bin_count":
-        # packed rectangles read (16 B per Gaussian); the [workgroup][tile] matrix (128 workgroups) is
-        # written, and read by the placement
-        return "hbm", n * 16.0 + st["tiles"] * 128 * 4.0 * 2
-    if stage == "tile_bins":
-        # placement reads the packed rectangle with the depth (16 B per Gaussian) and writes an 8-B key per
-        # overlap; the per-tile sort reads the key and writes a 4-B id
-        return "hbm", n * 16.0 + K * (8.0 + 8.0 + 4.0)
+    if stage in ("bin_count", "tile_bins"):
+        # both read the packed rectangles (16 B per Gaussian); the offset matrix [workgroup][tile] (one view: a
+        # workgroup per 1,024 Gaussians, at most 128) is written by the one and read by the other
+        both = n * 16.0 + st["tiles"] * min(128, max(1, -(-n // 1024))) * 4.0
+        # placement writes an 8-B key per overlap; the per-tile sort reads the key and writes a 4-B id
+        return "hbm", both + (K * (8.0 + 8.0 + 4.0) if stage == "tile_bins" else 0.0)
     if stage == "project":
         # parameters read; the 64-byte record slot, the packed rectangle word and the tile count written
         return "hbm", n * (56.0 + 64.0 + 16.0 + 4.0)
@@ -123,8 +121,8 @@ def read_traffic(stage: str, workload: str):
 
 # kernels of each stage, as rocprofv3 names them (prefix after the namespace)
 STAGE_KERNELS = {"render_bwd": ["k_render_bwd<10,"], "render_fwd": ["k_render_fwd<false>("],
-                 "tile_bins": ["k_bin_place(", "k_tile_sort<"],
-                 "bin_count": ["k_bin_count("],
+                 "tile_bins": ["k_bin_place(", "k_tile_sort("],
+                 "bin_count": ["k_bin_count<"],
                  "project": ["k_project("], "project_bwd_adam": ["k_project_bwd("],
                  "loss_ssim": ["k_loss_ssim("]}
 PMC_COMMANDS = {
@@ -216,8 +214,8 @@ VALU_PASSES = [
 N_CU = 256  # MI355X compute units
 # kernels of the tracking iteration, as rocprofv3 names them
 TRACK_KERNELS = {"render_bwd": ["k_render_bwd<6,"], "render_fwd": ["k_render_fwd<false>("],
-                 "project": ["k_project("], "project_bwd": ["k_project_bwd("], "bin_count": ["k_bin_count("],
-                 "tile_bins": ["k_bin_place(", "k_tile_sort<"],
+                 "project": ["k_project("], "project_bwd": ["k_project_bwd("], "bin_count": ["k_bin_count<"],
+                 "tile_bins": ["k_bin_place(", "k_tile_sort("],
                  "loss_track": ["k_select_hist(", "k_loss_track("]}
 PROFILE_COMMANDS = {
     "H": ("python3 bench.py --steps 5 --warmup 2 --no-cpu-baseline --no-tracking --no-batched --no-initnet "

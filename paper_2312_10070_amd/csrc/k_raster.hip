@@ -493,7 +493,7 @@ __device__ __forceinline__ f32x4 sums_of_hits(const BwdPix& b, const float (&wT)
 // Measured at 1200x680 with 500K Gaussians / 640x480 with 500K, six fields:
 // 267 / 146 us before (there a block walk, here one of per-quadrant lists with
 // LDS accumulators, both with workgroup batches and barriers), 175 / 118 us
-// now. On the way: the same sums with workgroup batches of 512 records 198 /
+// then, 169 / 107 now that tiles go by length (188 / 114 traced). On the way: the same sums with workgroup batches of 512 records 198 /
 // 149 us; visit lists per 4x4 quadrant (0.6 of the steps, but sums per
 // quadrant) with LDS float atomics 330 / 158 us, as those take about two
 // cycles per lane, with global atomics 1.1 ms / 344 us, as they need several
@@ -505,10 +505,10 @@ __device__ __forceinline__ f32x4 sums_of_hits(const BwdPix& b, const float (&wT)
 // depend on the order waves run in.
 //
 // ALPHA: with an upstream gradient of alpha. Its term gA = dL/dA T_fin is
-// subtracted from the suffix sum per pair: folded into the sum from the start,
-// as it may be for nothing, it had every addition rounded to its size (an alpha
-// gradient a thousand times the colour's, 200 layers: dL/do off by 2.1e-7 rms,
-// so 6.0e-8). A kernel of its own, as the operation costs the others 3 %.
+// subtracted from the suffix sum per pair. Folded into the sum from the start,
+// which takes no operation, it has every addition rounded to its size (an alpha
+// gradient a thousand times the colour's, 200 layers: dL/do off by 2.2e-7 rms,
+// so 5.4e-8). A kernel of its own, as the operation costs the others 3 %.
 template <int NF, BwdSums SUMS, bool ALPHA>
 __device__ __forceinline__ void bwd_item(const Raster& Rr, const BwdArgs& a, int item, BwdWave* smem) {
   constexpr int H = NF / 2;
