@@ -179,7 +179,7 @@ int gsr_render_bwd_adam(gsr_ctx *ctx, gsr_state *state, const float *dL_dcolor, 
                         const float *dL_dalpha, const gsr_adam5 *adam);
 
 /* Tile-shape autotuner for the batched path: times forward + backward (reps
- * runs after one warm-up, HIP events) for every tile shape in {16x16, 8x32,
+ * runs after a warm-up, HIP events) for every tile shape in {16x16, 8x32,
  * 32x8} and blocks_per_cu in {0, 1, 2, 4, 8} with the given upstream
  * gradients, writes the fastest shape into opts->tile_w / tile_h (the other
  * fields are inputs) and the fastest blocks_per_cu into *best_blocks_per_cu.
