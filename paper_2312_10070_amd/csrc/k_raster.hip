@@ -38,6 +38,8 @@
 // (see ItemOrder): one workgroup per item, or a persistent grid whose
 // workgroups pull items from a counter until the queue is empty
 // (multi-keyframe mapping).
+#include <type_traits>
+
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -714,14 +716,14 @@ __global__ __launch_bounds__(kTileThreads) void k_render_fwd_persistent(Raster R
   }
 }
 
-template <int NF, BwdSums SUMS>
+template <int NF, BwdSums SUMS, bool ALPHA>
 __global__ __launch_bounds__(kTileThreads, 5) void k_render_bwd_persistent(Raster Rr, BwdArgs a) {
   __shared__ BwdWave sm[kWavesPerTile];
   __shared__ int s_item;
   for (;;) {
     const int item = next_item(a.queue, a.order, a.n_items, &s_item);
     if (item < 0) break;
-    bwd_item<NF, SUMS, true>(Rr, a, item, sm);
+    bwd_item<NF, SUMS, ALPHA>(Rr, a, item, sm);
   }
 }
 
@@ -813,22 +815,24 @@ void launch_render_bwd(const Raster& R, const BwdArgs& a, hipStream_t s) {
   const bool queue = a.blocks > 0;
   const dim3 grid((unsigned)(queue ? a.blocks : a.n_items));
   if (queue) launch_fill_u32(reinterpret_cast<uint32_t*>(a.queue), 0u, 1, s);
-  auto go = [&](auto plain, auto alpha, auto many) {
+  auto go = [&](auto one, auto many) {
     if (queue) hipLaunchKernelGGL(many, grid, tb, 0, s, R, a);
-    else hipLaunchKernelGGL(a.gA ? alpha : plain, grid, tb, 0, s, R, a);
+    else hipLaunchKernelGGL(one, grid, tb, 0, s, R, a);
   };
-#define GSR_BWD(NF, SUMS) k_render_bwd<NF, SUMS, false>, k_render_bwd<NF, SUMS, true>, k_render_bwd_persistent<NF, SUMS>
+  auto with = [&](auto nf, auto sums) {
+    constexpr int NF = decltype(nf)::value;
+    constexpr BwdSums SUMS = decltype(sums)::value;
+    if (a.gA) go(k_render_bwd<NF, SUMS, true>, k_render_bwd_persistent<NF, SUMS, true>);
+    else go(k_render_bwd<NF, SUMS, false>, k_render_bwd_persistent<NF, SUMS, false>);
+  };
+  auto fields = [&](auto nf) {
+    if (det) with(nf, std::integral_constant<BwdSums, kStored>());
+    else if (a.wide) with(nf, std::integral_constant<BwdSums, kWide>());
+    else with(nf, std::integral_constant<BwdSums, kFloat>());
+  };
   // ten fields, or the six of a pose-only backward
-  if (a.geom_only) {
-    if (det) go(GSR_BWD(6, kStored));
-    else if (a.wide) go(GSR_BWD(6, kWide));
-    else go(GSR_BWD(6, kFloat));
-  } else {
-    if (det) go(GSR_BWD(10, kStored));
-    else if (a.wide) go(GSR_BWD(10, kWide));
-    else go(GSR_BWD(10, kFloat));
-  }
-#undef GSR_BWD
+  if (a.geom_only) fields(std::integral_constant<int, 6>());
+  else fields(std::integral_constant<int, 10>());
 }
 
 void launch_det_rev(const Raster& R, const int2* ranges, const uint32_t* ids, const int4* rect, const uint32_t* goff,
